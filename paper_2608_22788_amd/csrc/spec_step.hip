@@ -20,16 +20,25 @@
 //     gives exactly the sequential one.  The sampling row is a full
 //     vocabulary of fp32 probabilities per sequence, so the work is a
 //     streaming read of one or two rows:
-//       - accept_blocks_kernel: every 256-element block of every sequence's
-//         sampling row is summed by one wavefront (a float4 per lane, then a
-//         butterfly), so the whole chip shares the read even for a handful
-//         of sequences;
+//       - accept_blocks_kernel: every 1,024-element block of every sequence's
+//         sampling row is summed by one wavefront (exact float64
+//         accumulators, then a wavefront scan), so the whole chip shares the
+//         read even for a handful of sequences.  A block of 512 elements
+//         makes the walk and the cross-lane sum, which every wavefront pays,
+//         5 % of the call dearer (128 sequences x 151,936 tokens: 31.9
+//         against 30.3 us), and 8 sequences gain nothing;
 //       - accept_pick_kernel: one wavefront per sequence scans the block sums
 //         (lane runs of consecutive blocks, a wavefront scan of the run
 //         totals), finds the block where the cumulative mass first exceeds
-//         floor(u * total), and scans that block's 256 elements.
-//     Both kernels recompute the acceptance walk (2 gamma scalar loads)
-//     rather than pass it through memory.
+//         floor(u * total), then the lane run of 16 elements inside it and
+//         the element.
+//     The first kernel repeats the acceptance walk in every wavefront (two
+//     dependent loads); the second reads its result.
+//     Measured (151,936 tokens, 3 drafts, per call): 128 sequences 30.3 us
+//     against 89 us with the weights added one by one as 192-bit integers
+//     (block sums 86 -> 24 us; reading two rows of every sequence takes
+//     22 us); 8 sequences 11.3 us of kernel time against 17.4 us, a chain of
+//     memory latencies.
 //   Readings: probabilities are clamped to [0, 1] and uniforms to
 //   [0, 1 - 2^-24], NaN read as 0; a draft id outside [0, V) is rejected; if
 //   the leftover mass is zero the next token is drawn from p_k itself; a
@@ -46,7 +55,9 @@ namespace tsattn {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kBlk = 256;          // vocabulary elements per block (float4 per lane)
+constexpr int kQuads = 4;          // groups of 4 elements per lane of a block
+constexpr int kBlk = kWave * 4 * kQuads;   // vocabulary elements per block
+constexpr int kWsBlk = 256;        // elements per block sum in the workspace size
 constexpr int kPickThreads = 64;   // pick workgroup: one wavefront
 
 struct AppendParams {
@@ -143,11 +154,9 @@ __device__ __forceinline__ Fx fx_sub(Fx a, Fx b) {
     return r;
 }
 
-// A probability clamped to [0, 1] (NaN and negatives read as 0), in units of
-// 2^-149: significand M (with the implicit bit for normal numbers) shifted
-// left by (biased exponent - 1), at most 126.
+// A clamped probability in units of 2^-149: significand M (with the implicit
+// bit for normal numbers) shifted left by (biased exponent - 1), at most 126.
 __device__ __forceinline__ Fx fx_of_prob(float x) {
-    x = x > 0.0f ? fminf(x, 1.0f) : 0.0f;
     const uint32_t bits = __float_as_uint(x);
     const uint32_t e = bits >> 23, f = bits & 0x7fffffu;
     const uint64_t M = e ? (uint64_t)(f | 0x800000u) : (uint64_t)f;
@@ -199,122 +208,250 @@ __device__ __forceinline__ Fx fx_floor_mul(Fx Z, float u) {
     return Fx{out[0], out[1], out[2]};
 }
 
-__device__ __forceinline__ Fx fx_shfl_xor(Fx a, int m) {
-    return Fx{__shfl_xor(a.w0, m, kWave), __shfl_xor(a.w1, m, kWave), __shfl_xor(a.w2, m, kWave)};
-}
-__device__ __forceinline__ Fx fx_shfl_up(Fx a, int d) {
-    return Fx{__shfl_up(a.w0, d, kWave), __shfl_up(a.w1, d, kWave), __shfl_up(a.w2, d, kWave)};
-}
 __device__ __forceinline__ Fx fx_shfl(Fx a, int lane) {
     return Fx{__shfl(a.w0, lane, kWave), __shfl(a.w1, lane, kWave), __shfl(a.w2, lane, kWave)};
 }
 
-__device__ __forceinline__ Fx wave_sum(Fx x) {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1)
-        x = fx_add(x, fx_shfl_xor(x, m));
-    return x;
+// One step of a wavefront scan: the value CTRL moves into this lane, zero
+// where it moves none (rows outside kRows, or no source lane).
+template <int CTRL, int kRows>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t x) {
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, kRows, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, kRows, 0xf, false);
+    return (uint64_t)hi << 32 | lo;
+}
+template <int CTRL, int kRows>
+__device__ __forceinline__ Fx scan_step(Fx x) {
+    return fx_add(x, Fx{dpp_u64<CTRL, kRows>(x.w0), dpp_u64<CTRL, kRows>(x.w1), dpp_u64<CTRL, kRows>(x.w2)});
+}
+template <int CTRL, int kRows>
+__device__ __forceinline__ double scan_step(double x) {
+    return x + __longlong_as_double((long long)dpp_u64<CTRL, kRows>((uint64_t)__double_as_longlong(x)));
 }
 
-// Inclusive scan over a wavefront.
-__device__ __forceinline__ Fx wave_incl_scan(Fx x, int lane) {
+// Inclusive scan over a wavefront in vector-ALU lane moves (no LDS
+// round trips): four shifts inside each row of 16 lanes, then the last lane of
+// a row into the next row and the last lane of the lower half into the upper.
+constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+template <typename T>
+__device__ __forceinline__ T wave_incl_scan(T x) {
+    x = scan_step<kRowShr + 1, 0xf>(x);
+    x = scan_step<kRowShr + 2, 0xf>(x);
+    x = scan_step<kRowShr + 4, 0xf>(x);
+    x = scan_step<kRowShr + 8, 0xf>(x);
+    x = scan_step<kRowBcast15, 0xa>(x);
+    return scan_step<kRowBcast31, 0xc>(x);
+}
+
+// ---- exact sums in float64 ------------------------------------------------------
+// Adding every weight as an Fx costs about 60 instructions per element, which
+// made the streaming kernel bound by the vector ALU (128 sequences x 151,936
+// tokens: 86 us, 1.8 TB/s).  The weights are therefore summed in four float64
+// accumulators, each of which only ever holds multiples of a power of two and
+// stays below 2^53 of them, so that every addition is exact: multiples of
+// 2^-40 (sums up to 2^10), 2^-81, 2^-122 and 2^-149.  Adding and subtracting
+// 1.5 * 2^(52 - k) rounds a value to a multiple of 2^-k, and what is left over
+// (at most half of that) is exact and goes to the next accumulator.  Only
+// weights with bits below 2^-81 reach the last two, on a branch the whole
+// wavefront skips otherwise.  About 20 instructions per element, and v_add_f64
+// issues at the rate of v_add_f32.
+constexpr int kBinA = 40, kBinB = 81, kBinC = 122, kBinD = 149;
+struct Bins {
+    double a, b, c, d;
+};
+__device__ __forceinline__ Bins bins_zero() { return Bins{0.0, 0.0, 0.0, 0.0}; }
+
+template <int K>
+__device__ __forceinline__ double to_multiple(double x) {
+    constexpr double c = K == kBinA ? 0x1.8p12 : K == kBinB ? 0x1.8p-29 : 0x1.8p-70;   // 1.5 * 2^(52 - K)
+    return (x + c) - c;
+}
+
+__device__ __forceinline__ uint32_t high_word(double x) {
+    return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32);
+}
+
+// Adds the weights of four elements (clamped probabilities): w_j =
+// max(0, p_j - q_j) (kResid), else p_j.  p - min(p, q) is that weight; in
+// float64 it may round, and err is then the exact rest (p >= q).
+template <bool kResid>
+__device__ __forceinline__ void bins_add4(Bins &s, const float pe[4], const float qe[4]) {
+    double rest[4], err[4];
+    uint32_t small = 0;   // a nonzero value of this size has a nonzero high word
 #pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const Fx y = fx_shfl_up(x, d);
-        if (lane >= d)
-            x = fx_add(x, y);
+    for (int j = 0; j < 4; j++) {
+        const double p = pe[j];
+        double w = p;
+        err[j] = 0.0;
+        if constexpr (kResid) {
+            // values in [0, 1] order as their bits do
+            const double q = __uint_as_float(min(__float_as_uint(pe[j]), __float_as_uint(qe[j])));
+            w = p - q;
+            err[j] = (p - w) - q;
+            small |= high_word(err[j]);
+        }
+        const double ha = to_multiple<kBinA>(w);
+        const double lo = w - ha;
+        const double hb = to_multiple<kBinB>(lo);
+        s.a += ha;
+        s.b += hb;
+        rest[j] = lo - hb;
+        small |= high_word(rest[j]);
     }
-    return x;
+    if (__any(small != 0)) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const double eb = to_multiple<kBinB>(err[j]);
+            s.b += eb;
+            const double er = err[j] - eb;
+            const double c0 = to_multiple<kBinC>(rest[j]), c1 = to_multiple<kBinC>(er);
+            s.c += c0 + c1;
+            s.d += (rest[j] - c0) + (er - c1);
+        }
+    }
 }
 
+// x (a multiple of 2^-K, negative or not) in units of 2^-149, modulo 2^192.
+template <int K>
+__device__ __forceinline__ Fx fx_of_bin(double x) {
+    constexpr int sh = kBinD - K;   // 109, 68, 27, 0
+    int64_t n;
+    if constexpr (K == kBinA || K == kBinB) {
+        // x is below a third of this constant, so the sum keeps its exponent
+        // and counts the units in its significand
+        constexpr double c = K == kBinA ? 0x1.8p12 : 0x1.8p-29;
+        n = __double_as_longlong(x + c) - __double_as_longlong(c);
+    } else {
+        n = (int64_t)(K == kBinC ? x * 0x1p122 : (x * 0x1p75) * 0x1p74);
+    }
+    constexpr int o = sh & 63;
+    const uint64_t lo = (uint64_t)n << o, hi = o ? (uint64_t)(n >> ((64 - o) & 63)) : (uint64_t)(n >> 63);
+    const uint64_t sign = (uint64_t)(n >> 63);
+    return sh < 64 ? Fx{lo, hi, sign} : Fx{0, lo, hi};
+}
+__device__ __forceinline__ Fx fx_of_bins(const Bins &s) {
+    Fx r = fx_add(fx_of_bin<kBinA>(s.a), fx_of_bin<kBinB>(s.b));
+    if (__any(s.c != 0.0 || s.d != 0.0))
+        r = fx_add(r, fx_add(fx_of_bin<kBinC>(s.c), fx_of_bin<kBinD>(s.d)));
+    return r;
+}
+
+// The sum over the wavefront, in lane 63 (the other lanes hold partial sums).
+__device__ __forceinline__ Fx bins_wave_sum(Bins s) {
+    s.a = wave_incl_scan(s.a);
+    s.b = wave_incl_scan(s.b);
+    if (__any(s.c != 0.0 || s.d != 0.0)) {
+        s.c = wave_incl_scan(s.c);
+        s.d = wave_incl_scan(s.d);
+    }
+    return fx_of_bins(s);
+}
+
+// Read-only for the launch: through the constant address space, so that a
+// wavefront-uniform read is a scalar load.
+typedef const int32_t __attribute__((address_space(4))) *const_i32_ptr;
 __device__ __forceinline__ int clamp_gamma(const AcceptParams &a, int b) {
-    const int g = a.num_draft[b];
+    const int g = ((const_i32_ptr)a.num_draft)[b];
     return g < 0 ? 0 : (g > a.G ? a.G : g);
+}
+
+// A probability clamped to [0, 1] (NaN and negatives read as 0).
+__device__ __forceinline__ float clamp_prob(float x) {
+    return __uint_as_float(x > 0.0f ? min(__float_as_uint(x), 0x3f800000u) : 0u);
 }
 
 // Drafts accepted before the first rejection (gamma if none).  The test
 // u q <= p is exact: the product of two float32 values is exact in float64.
 // Every lane of the calling wavefront tests one draft (i = c + lane for
-// c = 0, 64, ...), so a walk costs two dependent loads per 64 drafts; the
-// first failing draft is the lowest set bit of the ballot.
-__device__ int accept_walk(const AcceptParams &a, int b) {
+// c = 0, 64, ...), so a walk costs two dependent loads per 64 drafts (the
+// drafts and uniforms do not wait for the draft count); the first failing
+// draft is the lowest set bit of the ballot.
+__device__ int accept_walk(const AcceptParams &a, int b, int gamma) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int gamma = clamp_gamma(a, b);
-    for (int c = 0; c < gamma; c += kWave) {
+    for (int c = 0; c < a.G; c += kWave) {
         const int i = c + lane;
+        int d = 0;
+        float u = 0.0f;
+        if (i < a.G) {
+            d = a.draft[(size_t)b * a.G + i];
+            u = clamp_uniform(a.u_accept[(size_t)b * a.G + i]);
+        }
         bool bad = false;
         if (i < gamma) {
-            const int d = a.draft[(size_t)b * a.G + i];
-            const float u = clamp_uniform(a.u_accept[(size_t)b * a.G + i]);
             if (d < 0 || d >= a.V) {
                 bad = true;
             } else {
-                const float pv = a.p[((size_t)b * (a.G + 1) + i) * a.V + d];
-                const float qv = a.q[((size_t)b * a.G + i) * a.V + d];
-                const float p = pv > 0.0f ? fminf(pv, 1.0f) : 0.0f;
-                const float q = qv > 0.0f ? fminf(qv, 1.0f) : 0.0f;
+                const float p = clamp_prob(a.p[((size_t)b * (a.G + 1) + i) * a.V + d]);
+                const float q = clamp_prob(a.q[((size_t)b * a.G + i) * a.V + d]);
                 bad = !((double)u * (double)q <= (double)p);
             }
         }
         const unsigned long long m = __ballot(bad);
         if (m)
             return c + __ffsll((long long)m) - 1;
+        if (c + kWave >= gamma)
+            break;
     }
     return gamma;
 }
 
-// Elements e .. e + 3 (zero past V) of the target row p_k and, when
-// `load_q`, of the draft row q_k.
-__device__ __forceinline__ void load_rows(const AcceptParams &a, int b, int k, bool load_q, int e, float pe[4],
-                                          float qe[4]) {
-    const float *prow = a.p + ((size_t)b * (a.G + 1) + k) * a.V;
-    const float *qrow = a.q + ((size_t)b * a.G + (load_q ? k : 0)) * a.V;
-    if (e + 3 < a.V && ((a.V & 3) == 0)) {
-        const float4 pv = *reinterpret_cast<const float4 *>(prow + e);
-        pe[0] = pv.x; pe[1] = pv.y; pe[2] = pv.z; pe[3] = pv.w;
-        if (load_q) {
-            const float4 qv = *reinterpret_cast<const float4 *>(qrow + e);
-            qe[0] = qv.x; qe[1] = qv.y; qe[2] = qv.z; qe[3] = qv.w;
-        } else {
-            qe[0] = qe[1] = qe[2] = qe[3] = 0.0f;
+// A lane's elements of a block: of the target row p_k and, at a rejection, of
+// the draft row q_k (else zero), clamped.
+struct Row {
+    float p[kQuads][4], q[kQuads][4];
+};
+
+// Elements e0 + step * i + j (i < kQuads, j < 4) of the block at `src`, where
+// `n` >= 1 elements of the row are left (zero past them; only the row's last
+// block is not whole).  A row starts on a 16-byte boundary only if V is a
+// multiple of 4; the loads ask for no more than the 4 bytes that every row
+// has.  kStream: the elements are read once, so the lines need not stay in
+// the caches (7 % of the call at 128 sequences x 151,936 tokens).
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <bool kStream>
+__device__ __forceinline__ void load_block(const float *src, int n, int e0, int step, float x[kQuads][4]) {
+    if (n >= kBlk) {   // wavefront-uniform
+#pragma unroll
+        for (int i = 0; i < kQuads; i++) {
+            const f4_any *at = reinterpret_cast<const f4_any *>(src + e0 + step * i);
+            const f4_any v = kStream ? __builtin_nontemporal_load(at) : *at;
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                x[i][j] = v[j];
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const bool in = e + j < a.V;
-            pe[j] = in ? prow[e + j] : 0.0f;
-            qe[j] = (in && load_q) ? qrow[e + j] : 0.0f;
-        }
-    }
-}
-
-// Exact sampling weights from the loaded elements: the leftover mass
-// max(0, p_k - q_k) (resid), else the target row itself.
-__device__ __forceinline__ void weights_of(const float pe[4], const float qe[4], bool resid, Fx w[4]) {
+        for (int i = 0; i < kQuads; i++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const Fx P = fx_of_prob(pe[j]);
-        if (resid) {
-            const Fx Q = fx_of_prob(qe[j]);
-            w[j] = fx_gt(P, Q) ? fx_sub(P, Q) : fx_zero();
-        } else {
-            w[j] = P;
-        }
+            for (int j = 0; j < 4; j++) {
+                const int e = e0 + step * i + j;
+                const float v = src[min(e, n - 1)];
+                x[i][j] = e < n ? v : 0.0f;
+            }
     }
 }
-
-// The weights of the sampling row at elements e .. e + 3: the leftover mass
-// at a rejection (use_p = false), else the target row.
-__device__ __forceinline__ void row_weights(const AcceptParams &a, int b, int k, bool rejected, bool use_p,
-                                           int e, Fx w[4]) {
-    const bool resid = rejected && !use_p;
-    float pe[4], qe[4];
-    load_rows(a, b, k, resid, e, pe, qe);
-    weights_of(pe, qe, resid, w);
+template <bool kResid, bool kStream>
+__device__ __forceinline__ void load_rows(const AcceptParams &a, int b, int k, int blk, int e0, int step, Row &r) {
+    const int first = blk * kBlk, n = a.V - first;
+    load_block<kStream>(a.p + ((size_t)b * (a.G + 1) + k) * a.V + first, n, e0, step, r.p);
+    if constexpr (kResid)
+        load_block<kStream>(a.q + ((size_t)b * a.G + k) * a.V + first, n, e0, step, r.q);
+#pragma unroll
+    for (int i = 0; i < kQuads; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            r.p[i][j] = clamp_prob(r.p[i][j]);
+            r.q[i][j] = kResid ? clamp_prob(r.q[i][j]) : 0.0f;
+        }
 }
 
-__device__ __forceinline__ Fx sum4(const Fx w[4]) {
-    return fx_add(fx_add(w[0], w[1]), fx_add(w[2], w[3]));
+template <bool kResid>
+__device__ __forceinline__ Bins sum_rows(const Row &r) {
+    Bins s = bins_zero();
+#pragma unroll
+    for (int i = 0; i < kQuads; i++)
+        bins_add4<kResid>(s, r.p[i], r.q[i]);
+    return s;
 }
 
 __device__ __forceinline__ void store_fx(uint64_t *p, Fx x) {
@@ -326,7 +463,7 @@ __device__ __forceinline__ Fx load_fx(const uint64_t *p) { return Fx{p[0], p[1],
 
 // Block sums j0 .. j0 + kPickChunk - 1 of a row (zero from `hi` on), every
 // load issued before any is used.
-constexpr int kPickChunk = 16;
+constexpr int kPickChunk = 4096 / kBlk;
 __device__ __forceinline__ void load_chunk(const uint64_t *bs, int j0, int hi, Fx v[kPickChunk]) {
 #pragma unroll
     for (int c = 0; c < kPickChunk; c++) {
@@ -336,42 +473,52 @@ __device__ __forceinline__ void load_chunk(const uint64_t *bs, int j0, int hi, F
 }
 
 // One wavefront per (sequence, block): the block's exact sum of sampling
-// weights.  The leftover-mass and plain-row sums are both written when a
-// rejection happened, so the pick kernel can fall back without another pass.
+// weights.  If a rejection's leftover mass is zero in the whole row, the pick
+// samples the target row, so a block without leftover mass stores the target
+// row's sum as well (when the row has any leftover mass nobody reads it).
+template <bool kResid>
+__device__ __forceinline__ void block_sum(const AcceptParams &a, int b, int k, int blk, int lane) {
+    Row r;
+    load_rows<kResid, true>(a, b, k, blk, 4 * lane, 4 * kWave, r);
+    const Fx s = bins_wave_sum(sum_rows<kResid>(r));
+    uint64_t *dst = a.bsum + ((size_t)b * 2 * a.nblk + blk) * 3;
+    if (lane == kWave - 1)
+        store_fx(dst, s);
+    if constexpr (kResid) {
+        if (__ballot(fx_is_zero(s)) >> (kWave - 1)) {
+            const Fx sp = bins_wave_sum(sum_rows<false>(r));
+            if (lane == kWave - 1)
+                store_fx(dst + (size_t)a.nblk * 3, sp);
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void accept_blocks_kernel(AcceptParams a) {
-    const int wave = (int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave));
     const int lane = threadIdx.x % kWave;
     if (wave >= a.B * a.nblk)
         return;
     const int b = wave / a.nblk, blk = wave % a.nblk;
     const int gamma = clamp_gamma(a, b);
-    const int k = accept_walk(a, b);
-    const bool rejected = k < gamma;
-    float pe[4], qe[4];
-    load_rows(a, b, k, rejected, blk * kBlk + 4 * lane, pe, qe);
-    Fx w[4];
-    weights_of(pe, qe, rejected, w);
-    const Fx s = wave_sum(sum4(w));
-    if (lane == 0)
-        store_fx(a.bsum + (((size_t)b * 2 + 0) * a.nblk + blk) * 3, s);
+    const int k = __builtin_amdgcn_readfirstlane(accept_walk(a, b, gamma));
     if (blk == 0 && lane == 0)
         a.walk[b] = k;   // read by the pick kernel, so it need not walk again
-    if (rejected) {
-        weights_of(pe, qe, false, w);   // the target row, from the same loads
-        const Fx sp = wave_sum(sum4(w));
-        if (lane == 0)
-            store_fx(a.bsum + (((size_t)b * 2 + 1) * a.nblk + blk) * 3, sp);
-    }
+    if (k < gamma)
+        block_sum<true>(a, b, k, blk, lane);
+    else
+        block_sum<false>(a, b, k, blk, lane);
 }
 
 // One wavefront per sequence: the total, the target T = floor(u Z), the block
-// whose cumulative mass first exceeds T, and the element inside it.  Since the
-// cumulative weights are integers, C_v > u Z exactly when C_v > T, and u < 1
-// makes T < Z, so the element exists and carries weight.
+// whose cumulative mass first exceeds T, the lane's run of elements inside it
+// and the element.  Since the cumulative weights are integers, C_v > u Z
+// exactly when C_v > T, and u < 1 makes T < Z, so the element exists and
+// carries weight.
 __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams a) {
     const int b = blockIdx.x;
     const int lane = threadIdx.x;
     const int gamma = clamp_gamma(a, b);
+    const float u = clamp_uniform(a.u_sample[b]);
     const int k = __builtin_amdgcn_readfirstlane(a.walk[b]);
     const bool rejected = k < gamma;
     const int per = (a.nblk + kWave - 1) / kWave;   // consecutive blocks per lane
@@ -393,7 +540,7 @@ __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams 
             for (int c = 0; c < kPickChunk; c++)
                 run = fx_add(run, v[c]);
         }
-        incl = wave_incl_scan(run, lane);
+        incl = wave_incl_scan(run);
         Z = fx_shfl(incl, kWave - 1);
         // leftover mass zero: sample p_k itself (its sums are in pass 1)
         if (pass == 0 && rejected && fx_is_zero(Z))
@@ -407,7 +554,7 @@ __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams 
         }
         return;
     }
-    const Fx T = fx_floor_mul(Z, clamp_uniform(a.u_sample[b]));
+    const Fx T = fx_floor_mul(Z, u);
 
     // the first lane whose run ends above T owns the block
     const unsigned long long own = __ballot(fx_gt(incl, T));
@@ -433,41 +580,48 @@ __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams 
         }
         base = acc;
     }
-    blk = __shfl(blk, owner, kWave);
+    blk = __builtin_amdgcn_readfirstlane(__shfl(blk, owner, kWave));
     base = fx_shfl(base, owner);
 
-    // the element inside that block
-    Fx w[4];
-    row_weights(a, b, k, rejected, pass == 1, blk * kBlk + 4 * lane, w);
-    const Fx lane_sum = sum4(w);
-    const Fx lincl = fx_add(base, wave_incl_scan(lane_sum, lane));
+    // the lane inside that block: each lane sums its run of 4 * kQuads elements
+    Row r;
+    Fx lane_sum;
+    if (rejected && pass == 0) {
+        load_rows<true, false>(a, b, k, blk, 4 * kQuads * lane, 4, r);
+        lane_sum = fx_of_bins(sum_rows<true>(r));
+    } else {
+        load_rows<false, false>(a, b, k, blk, 4 * kQuads * lane, 4, r);
+        lane_sum = fx_of_bins(sum_rows<false>(r));
+    }
+    const Fx lincl = fx_add(base, wave_incl_scan(lane_sum));
     const unsigned long long hit = __ballot(fx_gt(lincl, T));
     const int first = __ffsll((long long)hit) - 1;   // exists: the block's total exceeds T
-    int jsel = 3;
-    if (lane == first) {
-        // the smallest j whose cumulative weight exceeds T
-        Fx acc = fx_sub(lincl, lane_sum);
-        bool found = false;
+    const Fx before = fx_shfl(fx_sub(lincl, lane_sum), first);
+
+    // the element inside that run: lane m takes element m of it
+    float pm = 0.0f, qm = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-            acc = fx_add(acc, w[j]);
-            if (!found && fx_gt(acc, T)) {
-                jsel = j;
-                found = true;
-            }
-        }
+    for (int m = 0; m < 4 * kQuads; m++) {
+        const float pf = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r.p[m / 4][m % 4]), first));
+        const float qf = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r.q[m / 4][m % 4]), first));
+        pm = lane == m ? pf : pm;
+        qm = lane == m ? qf : qm;
     }
-    jsel = __shfl(jsel, first, kWave);
+    const Fx w = pm > qm ? fx_sub(fx_of_prob(pm), fx_of_prob(qm)) : fx_zero();
+    const Fx eincl = fx_add(before, wave_incl_scan(w));
+    const unsigned long long at = __ballot(fx_gt(eincl, T));
     if (lane == 0) {
         a.n_accepted[b] = k;
-        a.next_token[b] = blk * kBlk + 4 * first + jsel;
+        a.next_token[b] = blk * kBlk + 4 * kQuads * first + __ffsll((long long)at) - 1;
     }
 }
 
 }  // namespace
 
 // Workspace of the acceptance: the block sums, then (256-byte aligned) the
-// per-sequence walk results.
+// per-sequence walk results.  It holds two sums for every 256 elements; the
+// kernels use that for blocks of kBlk.
+static_assert(kBlk >= kWsBlk, "the block sums must fit the workspace");
 static size_t walk_offset(size_t num_seqs, size_t nblk) {
     return (num_seqs * 2 * nblk * 3 * sizeof(uint64_t) + 255) & ~(size_t)255;
 }
@@ -523,7 +677,7 @@ size_t ts_spec_accept_workspace_size(int32_t num_seqs, int32_t vocab) {
         fail(TS_ERR_ARG, "num_seqs and vocab must be positive");
         return 0;
     }
-    const size_t nblk = ((size_t)vocab + kBlk - 1) / kBlk;
+    const size_t nblk = ((size_t)vocab + kWsBlk - 1) / kWsBlk;
     return walk_offset(num_seqs, nblk) + (((size_t)num_seqs * sizeof(int32_t) + 255) & ~(size_t)255);
 }
 
@@ -556,14 +710,14 @@ int ts_spec_accept(int32_t num_seqs, int32_t vocab, int32_t max_draft, const flo
     a.next_token = next_token;
     a.bsum = static_cast<uint64_t *>(workspace);
     a.walk = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) +
-                                         walk_offset(num_seqs, ((size_t)vocab + kBlk - 1) / kBlk));
+                                         walk_offset(num_seqs, ((size_t)vocab + kWsBlk - 1) / kWsBlk));
     a.B = num_seqs;
     a.V = vocab;
     a.G = max_draft;
-    a.nblk = (vocab + kBlk - 1) / kBlk;
+    a.nblk = (int)(((int64_t)vocab + kBlk - 1) / kBlk);
     hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
     const int64_t waves = (int64_t)a.B * a.nblk;
-    if ((waves + 3) / 4 > INT32_MAX)
+    if (((int64_t)a.B * (((int64_t)vocab + kWsBlk - 1) / kWsBlk) + 3) / 4 > INT32_MAX)
         return fail(TS_ERR_ARG, "num_seqs x vocab is too large for one launch");
     const unsigned blocks = (unsigned)((waves + 3) / 4);
     hipLaunchKernelGGL(accept_blocks_kernel, dim3(blocks), dim3(256), 0, hs, a);

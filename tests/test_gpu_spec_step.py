@@ -146,6 +146,48 @@ def test_accept_many_sequences_full_vocabulary():
     check_against_oracle(p, q, d, nd, ua, us, "V151936xB64")
 
 
+# sizes at the edges of the 1,024-element blocks and of the four block sums a
+# lane of the pick keeps (256 blocks), odd ones among them
+@pytest.mark.parametrize("V", [1, 3, 1023, 1024, 1025, 4098, 262144, 262145])
+def test_accept_exact_over_the_float_range(V):
+    """Weights whose bits lie anywhere between 2^-149 and 1, within a row or
+    over the whole range, so that every accumulator of the exact sums and the
+    rounded differences p - q are reached; zero leftover in most blocks, in all
+    of them, dyadic rows with the uniform exactly on a boundary, and values
+    outside [0, 1]."""
+    rng = np.random.default_rng(V)
+    spans = [(-149, -127), (-140, -60), (-60, -20), (-149, 0), (-24, 0), (-70, -50)]
+    B, G = len(spans) + 4, 2
+    draw = lambda lo, hi, n: np.ldexp(1.0 + rng.random(n), rng.integers(lo, hi + 1, n)).astype(np.float32)  # noqa: E731
+    p = np.zeros((B, G + 1, V), np.float32)
+    q = np.zeros((B, G, V), np.float32)
+    for b, (lo, hi) in enumerate(spans):
+        for i in range(G + 1):
+            p[b, i] = draw(lo, hi, V)
+        for i in range(G):
+            q[b, i] = np.where(rng.random(V) < 0.5, draw(lo, hi, V), p[b, i] * np.float32(rng.random() + 0.4))
+    b = len(spans)
+    p[b:] = draw(-30, -10, V)
+    q[b:] = p[b:, :G]                              # no leftover mass at all ...
+    q[b + 1, :, V // 2] = 0.0                      # ... or only in one place
+    p[b + 2:] = np.float32(2.0 ** -18)             # equal dyadic weights
+    q[b + 2:] = np.float32(2.0 ** -19)
+    p[b + 3, :, ::3] = np.float32(np.nan)
+    p[b + 3, :, 1::5] = -1.0
+    p[b + 3, :, 2::7] = 3.0
+    d = np.full((B, G), V, np.int32)               # outside the vocabulary: rejected at 0
+    nd = np.full(B, G, np.int32)
+    d[::2, 0] = rng.integers(0, V, len(d[::2]))     # or accepted where u is 0, then rejected at 1
+    ua = np.zeros((B, G), np.float32)
+    for r in range(6):
+        us = rng.random(B).astype(np.float32)
+        us[b + 2] = np.float32(rng.integers(0, V) / V) if V & (V - 1) == 0 else us[b + 2]
+        us[r] = (0.0, 1.0, 2.0 ** -149, 1.0 - 2.0 ** -24, 0.5, np.nan)[r]
+        nd[1] = r % 3                              # the bonus row, the first row, the second
+        say(f"accept float range V={V} round {r}")
+        check_against_oracle(p, q, d, nd, ua, us, f"V{V}/{r}")
+
+
 def test_accept_golden_cases():
     """The hand-derived cases of the oracle's pins (each separates the exact
     rule from a rounded evaluation), run as one batch on the GPU."""
