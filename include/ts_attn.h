@@ -161,7 +161,8 @@ typedef struct ts_attn_plan {
     int32_t combine;            /* TS_COMBINE_* */
     int32_t grid;               /* workgroups of the streaming launch (workers, then any
                                    merge workgroups) */
-    int32_t threads;            /* threads per workgroup of the streaming launch */
+    int32_t threads;            /* threads per workgroup of the streaming launch (TS_VARIANT_WAVE:
+                                   64, or 256 where four wavefronts form a worker) */
     int32_t merge_blocks;       /* workgroups of the merge kernel (0 if none runs) */
     int64_t lds_bytes;          /* dynamic LDS per workgroup of the streaming launch */
     int64_t workspace_bytes;    /* ts_decode_attn_workspace_size(shape) */

@@ -23,6 +23,7 @@ namespace tsattn {
 
 kernel_fn decode_q1_variant(int D, int G);
 kernel_fn verify_variant(int D, int NB);
+kernel_fn verify_group_variant(int D, int NB, int *lds_bytes);
 kernel_fn verify_team_variant(int rows, int *lds_bytes, int *nbe);
 kernel_fn merge_variant(int D, bool few);
 int debug_check(const ts_attn_shape *s, const int32_t *page_table, const int32_t *ctx_lens,
@@ -75,6 +76,7 @@ int check_device() {
 struct Plan {
     bool q1;          // one-token VALU kernel, else a matrix-core verify kernel
     bool team;        // verify by four-wavefront teams sharing pages in LDS (head_dim 128)
+    bool group;       // single-wavefront streams in groups of four that share splits in LDS
     bool auto_w;      // worker count chosen by the library (W is then an upper bound)
     int G, NB, rows_per_unit, W;
     size_t ws_cnt_off, ws_dbg_off, ws_o_off, ws_lse_off, ws_bytes;
@@ -96,6 +98,18 @@ static int per_cu_bound(bool q1, bool team, int rows) {
     if (team)
         return 2;
     return rows <= 8 ? 4 : 3;
+}
+
+// Workers (workgroups of four wavefronts) of the group kernel: one per compute
+// unit, and no more than four pages' worth of the upper bound on the work (a
+// page per wavefront).  Two per compute unit stream slower (32 sequences,
+// q_len 1: 88.0 against 83.3 us; 4 with q_len 4: 24.8 against 22.0); eight
+// pages per worker lengthen the chain of the smallest calls (one sequence of
+// 1,600 tokens: 11.8 against 10.7 us).
+static int group_workers(const ts_attn_shape *s) {
+    const int64_t pages_ub = (int64_t)s->num_seqs * s->num_kv_heads *
+                             ((s->max_ctx_len + kPage - 1) / kPage);
+    return (int)std::min<int64_t>(256, (pages_ub + kGroupWaves - 1) / kGroupWaves);
 }
 
 static int auto_workers(const ts_attn_shape *s, bool q1, bool team, int rows) {
@@ -213,7 +227,20 @@ int make_plan(const ts_attn_shape *s, Plan *pl) {
     pl->team = !pl->q1 && s->head_dim == 128 &&
                (s->variant == TS_VARIANT_TEAM || (s->variant == TS_VARIANT_AUTO && pl->NB >= 3));
     pl->auto_w = s->num_workers == 0;
-    pl->W = s->num_workers > 0 ? s->num_workers : auto_workers(s, pl->q1, pl->team, pl->rows_per_unit);
+    // Everything else streams with single wavefronts, grouped four to a worker
+    // unless the caller asked for that kernel or fixed the worker count
+    // (head_dim 128 with three row blocks and more does not fit the group's
+    // registers).  Per call against single wavefronts as workers, whose every
+    // range writes its split pieces to memory: 256 sequences with 32 rows 296
+    // against 335 us, 64 with 24 rows 115 against 121, 4 with 16 rows 22
+    // against 26, 32 with 4 rows 82.5 against 85.2, 256 with 4 rows 552
+    // against 559; one sequence with 4 rows 10.7 against 10.6.
+    pl->group = !pl->q1 && !pl->team && pl->auto_w && s->variant == TS_VARIANT_AUTO &&
+                (pl->NB <= 2 || s->head_dim == 64);
+    if (s->num_workers > 0)
+        pl->W = s->num_workers;
+    else
+        pl->W = pl->group ? group_workers(s) : auto_workers(s, pl->q1, pl->team, pl->rows_per_unit);
     // Workspace: the split counters first, at a fixed size whatever the shape,
     // so that no call's partial results ever land on them (they are zero
     // between calls); then 256 bytes for the TS_DEBUG check's flag word; then
@@ -268,6 +295,11 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
         L.main_k = verify_team_variant(pl.rows_per_unit, &extra, &nbe);
         L.main_lds = ((L.lds + 15) & ~(size_t)15) + (size_t)extra;
         L.main_threads = 4 * kWave;
+    } else if (pl.group) {
+        int extra = 0;
+        L.main_k = verify_group_variant(D, pl.NB, &extra);
+        L.main_lds = ((L.lds + 15) & ~(size_t)15) + (size_t)extra;
+        L.main_threads = kGroupWaves * kWave;
     } else {
         L.main_k = verify_variant(D, pl.NB);
     }
@@ -280,8 +312,9 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
             pl.W = resident;
     }
     // Who combines the splits (attn_split.h):
-    //  * the last worker of a unit, for the single-wavefront kernels with at
-    //    least twice as many units as workers (a unit has one or two pieces);
+    //  * the last worker of a unit, for the single-wavefront and group kernels
+    //    with at least twice as many units as workers (a unit has one or two
+    //    pieces);
     //  * merge wavefronts appended to the grid, one per row of each unit, when
     //    units have many pieces (a unit meets about W / units + 1 workers;
     //    here W >= 8 units) and that takes at most kMaxMergeWgs workgroups;
@@ -293,17 +326,26 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
     // workload (4 sequences, 64 rows).  With 1,024 merge wavefronts (8
     // sequences with q_len 4, the MTP workload) it was 1-2 % slower, and so
     // was it with 2-4 pieces per unit (64-128 sequences), hence the bounds.
-    constexpr int64_t kMaxMergeWgs = 512;
+    // A group's merge workgroup takes four rows and a group leaves fewer
+    // pieces, so for groups the workgroup count alone decides: at 128-256
+    // merge workgroups (4-8 sequences with q_len 4) it is 1.2-1.5 us faster
+    // than the merge kernel, at 448 0.8 us, at 640 1.9 us slower.  Two such
+    // workgroups fit on a compute unit, so with at most 256 of them one call
+    // never holds every slot of an XCD with wavefronts that wait.  Past that,
+    // from two units a worker the last arriver combines (256 sequences with
+    // 32 rows: 297.9 against 299.9 us with the merge kernel); at one unit a
+    // worker it was 3-7 % slower than the merge kernel.
+    const int64_t kMaxMergeWgs = pl.group ? 256 : 512;
     const size_t o_bytes = pl.ws_lse_off - pl.ws_o_off;
     const int64_t units = (int64_t)B * Hkv;
     const int ngroups = (pl.rows_per_unit + 3) / 4;
-    const int64_t merge_wgs = units * (pl.team ? ngroups : pl.rows_per_unit);
+    const int64_t merge_wgs = units * (pl.team || pl.group ? ngroups : pl.rows_per_unit);
     L.combine = kCombineKernel;
     if (o_bytes < ((size_t)1 << 31)) {
-        if (!pl.team && units >= 2 * (int64_t)pl.W)
-            L.combine = kCombineLast;
-        else if ((int64_t)pl.W >= 8 * units && merge_wgs <= kMaxMergeWgs)
+        if ((pl.group || (int64_t)pl.W >= 8 * units) && merge_wgs <= kMaxMergeWgs)
             L.combine = kCombineInLaunch;
+        else if (!pl.team && units >= 2 * (int64_t)pl.W)
+            L.combine = kCombineLast;
     }
     L.ws_o_bytes = L.combine != kCombineKernel ? (int)o_bytes : 0;
     // Counters of consecutive units up to 4 KiB apart (inside the counter

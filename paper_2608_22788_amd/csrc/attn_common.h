@@ -28,6 +28,7 @@ namespace tsattn {
 
 constexpr int kPage = 16;          // tokens per page
 constexpr int kWave = 64;          // CDNA wavefront width
+constexpr int kGroupWaves = 4;     // wavefronts of a group (attn_verify.hip)
 constexpr int kMaxSeqs = 4096;     // sequences per call (LDS prefix array)
 constexpr int kMaxUnits = 1 << 18; // (sequence, KV head) units per call
 constexpr size_t kCounterBytes = (size_t)kMaxUnits * sizeof(int);   // split counters
@@ -142,6 +143,15 @@ __device__ __forceinline__ float sum8(float x) {
 }
 
 __device__ __forceinline__ int first_lane_int(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// A value that is the same in every lane, as a scalar.  What is read from the
+// page prefix in LDS arrives in vector registers; K/V loads whose buffer
+// resource depends on it would otherwise be issued from a loop over the lanes'
+// values.
+__device__ __forceinline__ int64_t first_lane_int64(int64_t x) {
+    const uint32_t lo = (uint32_t)first_lane_int((int)(uint32_t)x);
+    return (int64_t)first_lane_int((int)(x >> 32)) << 32 | lo;
+}
 
 // Split counter of unit (b, g).
 __device__ __forceinline__ int *unit_counter(const AttnParams &p, int unit) {
@@ -264,14 +274,15 @@ __device__ __forceinline__ Segment locate(const AttnParams &p, const int *s_pre,
                                           int64_t range_end) {
     Segment s;
     s.b = first_lane_int(find_seq(s_pre, p.B, x, p.Hkv));
-    const int np = s_pre[s.b + 1] - s_pre[s.b];
-    const int64_t base = (int64_t)p.Hkv * s_pre[s.b];
+    const int first = first_lane_int(s_pre[s.b]);
+    const int np = first_lane_int(s_pre[s.b + 1]) - first;
+    const int64_t base = (int64_t)p.Hkv * first;
     const int64_t off = x - base;
     s.g = first_lane_int((int)(off / np));
     s.j0 = first_lane_int((int)(off % np));
     const int64_t unit_end = base + (int64_t)(s.g + 1) * np;
     const int64_t seg_end = unit_end < range_end ? unit_end : range_end;
-    s.j1 = s.j0 + (int)(seg_end - x);
+    s.j1 = first_lane_int(s.j0 + (int)(seg_end - x));
     s.whole = (s.j0 == 0) && (seg_end == unit_end);
     s.np = np;
     s.us = base + (int64_t)s.g * np;

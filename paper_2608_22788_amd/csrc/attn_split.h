@@ -205,16 +205,17 @@ __device__ __forceinline__ void write_merged(const AttnParams &p, int b, int g, 
         *reinterpret_cast<uint2 *>(dst) = make_uint2(w2[0], w2[1]);
 }
 
-// Combines all pieces of unit (b, g) and writes its rows (one wavefront;
-// rows_per_unit rows, 4 per pass; rows of draft positions >= q_len are
-// skipped).  Called by the worker that counted the last arrival on the unit,
-// which then sets the counter back to zero for the next call.
+// Combines all pieces of unit (b, g) and writes its rows (4 per pass and
+// wavefront, from row `first`, `step` apart; rows of draft positions >= q_len
+// are skipped).  Called by the worker that counted the last arrival on the
+// unit, which then sets the counter back to zero for the next call.
 template <int D>
-__device__ void combine_unit(const AttnParams &p, int b, int g, const UnitSplit &u, int lane) {
+__device__ void combine_unit(const AttnParams &p, int b, int g, const UnitSplit &u, int lane, int first = 0,
+                             int step = 4) {
     const int part = lane & 15;
     const int R = p.rows_per_unit;
     const int Q = ld_meta(p.q_lens, b);
-    for (int r0 = 0; r0 < R; r0 += 4) {
+    for (int r0 = first; r0 < R; r0 += step) {
         const int r = r0 + (lane >> 4);
         const bool row_ok = r < R && r / p.G < Q;
         Acc<D / 16> a;
@@ -262,6 +263,49 @@ struct Arrivals {
             else
                 u1 = u;
         }
+    }
+    // The same for a group of wavefronts, which writes at most two partials:
+    // of the unit its range starts in and of the one it ends in.
+    __device__ __forceinline__ void add_unit(const AttnParams &p, int u) {
+        if (p.combine != kCombineKernel) {
+            if (u0 < 0)
+                u0 = u;
+            else
+                u1 = u;
+        }
+    }
+    // kCombineLast for a workgroup of kGroupWaves wavefronts: the arrivals of
+    // both units are counted at once, and the workgroup that counted a unit's
+    // last one combines it.  `last`: two ints of LDS.
+    template <int D>
+    __device__ __forceinline__ void combine_last(const AttnParams &p, const int *s_pre, int64_t ptot, int *last) {
+        if (u0 < 0)
+            return;
+        wait_vmem();
+        __syncthreads();   // every wavefront's stores are complete
+        if (threadIdx.x < 2) {
+            const int unit = threadIdx.x ? u1 : u0;
+            int mine = 0;
+            if (unit >= 0) {
+                const int old = atomicAdd(unit_counter(p, unit), 1);
+                mine = old == split_of(p, s_pre, unit, ptot).nparts - 1;
+            }
+            last[threadIdx.x] = mine;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            if (!first_lane_int(last[k]))
+                continue;
+            const int unit = k ? u1 : u0;
+            combine_unit<D>(p, unit / p.Hkv, unit % p.Hkv, split_of(p, s_pre, unit, ptot),
+                            (int)(threadIdx.x & (kWave - 1)), 4 * (int)(threadIdx.x / kWave), 4 * kGroupWaves);
+        }
+    }
+    __device__ static UnitSplit split_of(const AttnParams &p, const int *s_pre, int unit, int64_t ptot) {
+        const int b = unit / p.Hkv, g = unit % p.Hkv;
+        const int np = s_pre[b + 1] - s_pre[b];
+        return unit_split(ptot, (int64_t)p.Hkv * s_pre[b] + (int64_t)g * np, np, p.W);
     }
     // Called by every thread of the workgroup; the first thread counts.
     template <bool kBlock>
@@ -318,7 +362,7 @@ __device__ void combine_waves(Acc<VE> &a, float *comb, int wave, int lane) {
 //
 // The grid holds the W workers and then the merge workgroups, one wavefront
 // per row of each unit (single-wavefront kernels: workgroup W + m is row
-// m % R of unit m / R; four-wavefront kernels: wave w of workgroup W + m is
+// m % R of unit m / R; group and team kernels: wave w of workgroup W + m is
 // row 4 (m % ceil(R / 4)) + w of unit m / ceil(R / 4)).  A merge wavefront
 // waits until every worker with a piece of its unit has counted its arrival,
 // then its four 16-lane groups read pieces k, k + 4, ... (k = lane / 16)
@@ -359,22 +403,24 @@ __device__ __forceinline__ bool wait_count(const int *c, int target) {
 
 // Sums of the four 16-lane groups (same part, different pieces) combined;
 // every group gets the total.
+template <typename F>
+__device__ __forceinline__ float across_lane_groups(float x, F f) {
+    // both operands x: the swap leaves rows {0, 0, 2, 2} and {1, 1, 3, 3},
+    // then halves {0, 0} and {1, 1} (vector-ALU moves, no LDS round trip)
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
 template <int VE>
 __device__ __forceinline__ void combine_lane_groups(Acc<VE> &a) {
-    float Mall = fmaxf(a.M, __shfl_xor(a.M, 16));
-    Mall = fmaxf(Mall, __shfl_xor(Mall, 32));
+    const auto add = [](float x, float y) { return x + y; };
+    const float Mall = across_lane_groups(a.M, [](float x, float y) { return fmaxf(x, y); });
     const float f = a.M == -INFINITY ? 0.0f : fast_exp2(a.M - Mall);
-    float den = a.den * f;
-    den += __shfl_xor(den, 16);
-    den += __shfl_xor(den, 32);
-    a.den = den;
+    a.den = across_lane_groups(a.den * f, add);
 #pragma unroll
-    for (int e = 0; e < VE; e++) {
-        float v = a.acc[e] * f;
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        a.acc[e] = v;
-    }
+    for (int e = 0; e < VE; e++)
+        a.acc[e] = across_lane_groups(a.acc[e] * f, add);
     a.M = Mall;
 }
 

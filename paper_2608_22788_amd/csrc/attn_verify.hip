@@ -39,6 +39,10 @@
 // Splits are combined as p.combine says (attn_split.h): by the last worker to
 // finish a piece of the unit, by the merge wavefronts that follow the workers
 // in the grid (workgroups W and up), or by the separate merge kernel.
+//
+// Two kernels share this code: verify_kernel, where a wavefront is a worker,
+// and verify_group_kernel (the automatic choice), where four are and the
+// pieces of a unit that they share meet in LDS first.
 #include "attn_split.h"
 
 namespace tsattn {
@@ -229,11 +233,74 @@ struct Verify {
         }
     }
 
+    // A piece of a split unit as one wavefront of a group leaves it in LDS:
+    // the sums of P V relative to 2^m in the wavefront's own lane order (so
+    // that writes and reads are free of bank conflicts), and where they go.
+    struct Rec {
+        float4 acc[NB][4][VE / 4][kWave];
+        float m[16 * NB], l[16 * NB];
+        int unit, b, g, Q;   // unit -1: no piece
+        int slot;            // slot of the group's partial, -1: the unit lies in the group's range
+    };
+    // The LDS of a group: wavefront w owns records 2 w (a split piece that
+    // starts its range) and 2 w + 1 (a later one).
+    struct GroupLds {
+        Rec rec[2 * kGroupWaves];
+        int last[2];         // kCombineLast: whether this group combines its split units
+    };
+    // A wavefront's view of its group.
+    struct Group {
+        GroupLds *lds;
+        int wg;              // the group's worker index
+        int64_t begin, end;  // its global pages
+        __device__ void locate(const AttnParams &p, int64_t ptot) {
+            begin = first_lane_int64(worker_begin(ptot, wg, p.W));
+            end = first_lane_int64(worker_begin(ptot, wg + 1, p.W));
+        }
+    };
+
+    // Leaves segment c's sums in the wavefront's record slot_id & 1.
+    __device__ static void finish_rec(const AttnParams &p, const Cur &c, const State &st, int slot_id,
+                                      const Group &gr, int n, int kq) {
+        Rec &rec = gr.lds->rec[2 * (int)(threadIdx.x / kWave) + (slot_id & 1)];
+        const int lane = 16 * kq + n;
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+#pragma unroll
+                for (int e = 0; e < VE; e += 4)
+                    rec.acc[rb][i][e / 4][lane] = make_float4(st.acc[rb][e][i], st.acc[rb][e + 1][i],
+                                                              st.acc[rb][e + 2][i], st.acc[rb][e + 3][i]);
+                if (n == 0)
+                    rec.l[rb * 16 + 4 * kq + i] = st.lacc[rb][i];
+            }
+            if (kq == 0)
+                rec.m[rb * 16 + n] = st.m_ref[rb];
+        }
+        if (lane == 0) {
+            rec.unit = c.s.b * p.Hkv + c.s.g;
+            rec.b = c.s.b;
+            rec.g = c.s.g;
+            rec.Q = c.Q;
+            rec.slot = c.s.us >= gr.begin && c.s.us + c.s.np <= gr.end ? -1
+                                                                       : 2 * gr.wg + (c.s.us > gr.begin ? 1 : 0);
+        }
+    }
+
     // Writes segment c's rows: to `out` when the segment is its whole unit,
-    // else as a normalised partial with its log2-sum-exp in slot slot_id.
+    // else (kGroup) to an LDS record, or as a normalised partial with its
+    // log2-sum-exp in slot slot_id.
+    template <bool kGroup>
     __device__ static void finish(const AttnParams &p, const Cur &c, const State &st, int slot_id, int64_t ptot,
-                                  int n, int kq) {
+                                  const Group &gr, int n, int kq) {
         const int b = c.s.b, g = c.s.g, G = p.G, R = p.rows_per_unit, Q = c.Q;
+        if constexpr (kGroup) {
+            if (!c.s.whole) {
+                finish_rec(p, c, st, slot_id, gr, n, kq);
+                return;
+            }
+        }
         // lane holds rows 16 rb + 4 kq + i, dims VE n .. VE n + VE - 1
 #pragma unroll
         for (int rb = 0; rb < NB; rb++) {
@@ -256,7 +323,7 @@ struct Verify {
                         *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
                     else
                         *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
-                } else {
+                } else if constexpr (!kGroup) {
                     const size_t row = (size_t)slot_id * R + r;
                     float *dst = p.ws_o + row * D + VE * n;
                     const float lse = l > 0.0f ? m + __log2f(l) : -INFINITY;
@@ -281,15 +348,17 @@ struct Verify {
                 }
             }
         }
-        if (!c.s.whole && p.combine == kCombineLast)
-            arrive_and_combine<D>(p, c.s, ptot, threadIdx.x);
+        if constexpr (!kGroup)
+            if (!c.s.whole && p.combine == kCombineLast)
+                arrive_and_combine<D>(p, c.s, ptot, threadIdx.x);
     }
 
     // One segment on its own, the page after the current one in flight
     // within the segment (the layout for two or more row blocks, which have
     // no registers to spare for a pipeline across segments).
-    __device__ static void segment(const AttnParams &p, const Segment &s, int slot_id, int64_t ptot) {
-        const int lane = threadIdx.x;
+    template <bool kGroup>
+    __device__ static void segment(const AttnParams &p, const Segment &s, int slot_id, int64_t ptot, const Group &gr) {
+        const int lane = threadIdx.x & (kWave - 1);
         const int n = lane & 15;
         const int kq = lane >> 4;
         const int G = p.G, R = p.rows_per_unit;
@@ -327,7 +396,7 @@ struct Verify {
                 }
             }
         }
-        finish(p, c, st, slot_id, ptot, n, kq);
+        finish<kGroup>(p, c, st, slot_id, ptot, gr, n, kq);
     }
 
     // Streams the worker's global pages [begin, end) with one row block as
@@ -336,9 +405,10 @@ struct Verify {
     // The next segment is located, its lengths read and its query rows
     // loaded when the current one starts, so a unit boundary costs the
     // epilogue and no refill of the pipeline.
+    template <bool kGroup>
     __device__ static void run(const AttnParams &p, const int *s_pre, int64_t begin, int64_t end, int w,
-                               int64_t ptot, Arrivals &arr) {
-        const int lane = threadIdx.x;
+                               int64_t ptot, Arrivals &arr, Group gr) {
+        const int lane = threadIdx.x & (kWave - 1);
         const int n = lane & 15;
         const int kq = lane >> 4;
         Cur c;
@@ -351,6 +421,8 @@ struct Verify {
         bool more = c.s.next < end;
         State st;
         start(p, c, q, st, n);
+        if constexpr (kGroup)
+            gr.locate(p, ptot);   // while the first page is on its way
         if (more) {
             head(p, locate(p, s_pre, c.s.next, end), nx);
             load_q(p, nx.s.b, nx.s.g, n, kq, q);
@@ -369,8 +441,9 @@ struct Verify {
                 load_block(p, ld_meta(tpt, tj), !last || more, to_next ? nx.s.g : c.s.g, n, kq, ring[1 - k]);
                 page_step(p, st, ring[k], j, c.full_end, c.seg_end_tok, kq);
                 if (last) {
-                    finish(p, c, st, slot_id, ptot, n, kq);
-                    arr.add(p, c.s);
+                    finish<kGroup>(p, c, st, slot_id, ptot, gr, n, kq);
+                    if constexpr (!kGroup)
+                        arr.add(p, c.s);
                     if (!more)
                         return;
                     slot_id = 2 * w + 1;
@@ -388,6 +461,109 @@ struct Verify {
             }
         }
     }
+
+    // Combines the records of a group whose wavefronts have all met: the
+    // pieces of a unit that lies in the group's range go to `out`, those of
+    // a unit that other groups share become one partial of the group.  Thread
+    // (row, part) = (tid / 16, tid % 16) owns VE dims of a row per row block.
+    // A unit has at most one record per wavefront; all of them are read at
+    // once, so a unit costs one LDS latency (walking the records one by one
+    // took 1.2-3.3 us here, half of what the group saves).
+    __device__ static void combine_group(const AttnParams &p, const GroupLds &gl, Arrivals &arr) {
+        const int G = p.G, R = p.rows_per_unit, part = threadIdx.x & 15;
+        const int r16 = threadIdx.x >> 4, lane = threadIdx.x & (kWave - 1);
+        int di[NB], hl[NB];
+#pragma unroll
+        for (int rb = 0; rb < NB; rb++) {
+            di[rb] = (rb * 16 + r16) / G;
+            hl[rb] = (rb * 16 + r16) % G;
+        }
+        __syncthreads();
+        const int unit_of = lane < 2 * kGroupWaves ? gl.rec[lane & (2 * kGroupWaves - 1)].unit : -1;
+        uint32_t todo = (uint32_t)__ballot(unit_of >= 0);
+        while (todo) {
+            const int k0 = __builtin_ctz(todo);
+            const int unit = __builtin_amdgcn_readlane(unit_of, k0);
+            uint32_t same = (uint32_t)__ballot(unit_of == unit);
+            todo &= ~same;
+            const int b = first_lane_int(gl.rec[k0].b), g = first_lane_int(gl.rec[k0].g);
+            const int Q = first_lane_int(gl.rec[k0].Q), slot = first_lane_int(gl.rec[k0].slot);
+            int ks[kGroupWaves];
+            bool on[kGroupWaves];
+#pragma unroll
+            for (int k = 0; k < kGroupWaves; k++) {
+                on[k] = same != 0;
+                ks[k] = same ? __builtin_ctz(same) : k0;
+                same &= same - 1;
+            }
+#pragma unroll
+            for (int rb = 0; rb < NB; rb++) {
+                const int r = rb * 16 + r16;
+                float m[kGroupWaves], l[kGroupWaves];
+                float4 v[kGroupWaves][VE / 4];
+#pragma unroll
+                for (int k = 0; k < kGroupWaves; k++) {
+                    const Rec &rec = gl.rec[ks[k]];
+                    m[k] = on[k] ? rec.m[r] : -INFINITY;
+                    l[k] = rec.l[r];
+#pragma unroll
+                    for (int e = 0; e < VE / 4; e++)
+                        v[k][e] = rec.acc[rb][r16 & 3][e][16 * (r16 >> 2) + part];
+                }
+                float M = m[0];
+#pragma unroll
+                for (int k = 1; k < kGroupWaves; k++)
+                    M = fmaxf(M, m[k]);
+                Acc<VE> a;
+                a.init();
+#pragma unroll
+                for (int k = 0; k < kGroupWaves; k++) {
+                    const float f = m[k] == -INFINITY ? 0.0f : fast_exp2(m[k] - M);
+                    a.den += f * l[k];
+#pragma unroll
+                    for (int e = 0; e < VE / 4; e++) {
+                        a.acc[4 * e + 0] += f * v[k][e].x;
+                        a.acc[4 * e + 1] += f * v[k][e].y;
+                        a.acc[4 * e + 2] += f * v[k][e].z;
+                        a.acc[4 * e + 3] += f * v[k][e].w;
+                    }
+                }
+                if (r >= R || di[rb] >= Q)
+                    continue;
+                const float inv = a.den > 0.0f ? 1.0f / a.den : 0.0f;
+                if (slot < 0) {
+                    uint16_t *dst = p.out + (((size_t)b * p.Qmax + di[rb]) * p.Hq + (size_t)g * G + hl[rb]) * D + VE * part;
+                    uint32_t w[VE / 2];
+#pragma unroll
+                    for (int e = 0; e < VE / 2; e++)
+                        w[e] = pack_bf16x2(a.acc[2 * e] * inv, a.acc[2 * e + 1] * inv);
+                    if constexpr (VE == 8)
+                        *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+                    else
+                        *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
+                    continue;
+                }
+                const float lse = a.den > 0.0f ? M + __log2f(a.den) : -INFINITY;
+                const size_t row = (size_t)slot * R + r;
+#pragma unroll
+                for (int e = 0; e < VE; e += 4) {
+                    const f32x4_t o = {a.acc[e] * inv, a.acc[e + 1] * inv, a.acc[e + 2] * inv, a.acc[e + 3] * inv};
+                    if (p.combine != kCombineKernel)
+                        st_partial16(p, row * D + VE * part + e, o);
+                    else
+                        *reinterpret_cast<f32x4_t *>(p.ws_o + row * D + VE * part + e) = o;
+                }
+                if (part == 0) {
+                    if (p.combine != kCombineKernel)
+                        st_coherent(p.ws_lse + row, lse);
+                    else
+                        p.ws_lse[row] = lse;
+                }
+            }
+            if (slot >= 0)
+                arr.add_unit(p, unit);
+        }
+    }
 };
 
 template <int D, int NB>
@@ -399,7 +575,7 @@ __global__ __launch_bounds__(64) void verify_kernel(AttnParams p) {
         merge_in_launch<D>(p, s_pre, m / p.rows_per_unit, m % p.rows_per_unit);
         return;
     }
-    const int64_t ptot = (int64_t)p.Hkv * s_pre[p.B];
+    const int64_t ptot = (int64_t)p.Hkv * first_lane_int(s_pre[p.B]);
     const int w = xcd_worker(blockIdx.x, p.W);
     const int64_t begin = worker_begin(ptot, w, p.W);
     const int64_t end = worker_begin(ptot, w + 1, p.W);
@@ -407,11 +583,11 @@ __global__ __launch_bounds__(64) void verify_kernel(AttnParams p) {
     arr.init();
     if constexpr (NB == 1) {
         if (begin < end)
-            Verify<D, NB>::run(p, s_pre, begin, end, w, ptot, arr);
+            Verify<D, NB>::template run<false>(p, s_pre, begin, end, w, ptot, arr, {});
     } else {
         for (int64_t x = begin; x < end;) {
             const Segment s = locate(p, s_pre, x, end);
-            Verify<D, NB>::segment(p, s, x == begin ? 2 * w : 2 * w + 1, ptot);
+            Verify<D, NB>::template segment<false>(p, s, x == begin ? 2 * w : 2 * w + 1, ptot, {});
             arr.add(p, s);
             x = s.next;
         }
@@ -419,9 +595,70 @@ __global__ __launch_bounds__(64) void verify_kernel(AttnParams p) {
     arr.flush<false>(p);
 }
 
+// Groups: a workgroup of kGroupWaves wavefronts is one worker.  Its range of
+// pages is dealt to the wavefronts as the call's is to the workers (wavefront
+// v of group w takes range kGroupWaves w + v of kGroupWaves W), each streams
+// its share as a single-wavefront worker does, and the pieces of units that
+// several of them share meet in LDS.  That leaves a quarter of the partials to
+// write, read back and wait for: at 256 sequences x 32 rows (1,024 units) the
+// single wavefronts wrote 28 MB of them next to 1.9 GB of K/V and a merge
+// kernel read them (335 us; groups 296 us), and at 4 sequences x 16 rows half
+// of the 26 us went to the pieces' way through memory (groups 22 us).
+template <int D, int NB>
+__global__ __launch_bounds__(kGroupWaves * kWave, NB == 1 ? 2 : 1) void verify_group_kernel(AttnParams p) {
+    extern __shared__ int s_pre[];
+    typedef Verify<D, NB> V;
+    page_prefix(p, s_pre);
+    if (__builtin_expect((int)blockIdx.x >= p.W, 0)) {   // merge workgroups, laid out after the workers' code
+        const int m = (int)blockIdx.x - p.W, ngroups = (p.rows_per_unit + 3) / 4;
+        merge_in_launch<D>(p, s_pre, m / ngroups, 4 * (m % ngroups) + (int)(threadIdx.x / kWave));
+        return;
+    }
+    auto &gl = *reinterpret_cast<typename V::GroupLds *>(reinterpret_cast<char *>(s_pre) +
+                                                         (((p.B + 1) * 4 + 15) & ~15));
+    const int wave = first_lane_int((int)(threadIdx.x / kWave));
+    if ((threadIdx.x & (kWave - 1)) < 2)
+        gl.rec[2 * wave + (threadIdx.x & (kWave - 1))].unit = -1;
+    const int64_t ptot = (int64_t)p.Hkv * first_lane_int(s_pre[p.B]);
+    const int wg = xcd_worker(blockIdx.x, p.W), w = kGroupWaves * wg + wave;
+    const int64_t begin = first_lane_int64(worker_begin(ptot, w, kGroupWaves * p.W));
+    const int64_t end = first_lane_int64(worker_begin(ptot, w + 1, kGroupWaves * p.W));
+    typename V::Group gr{&gl, wg, 0, 0};
+    Arrivals arr;
+    arr.init();
+    if constexpr (NB == 1) {
+        if (begin < end)
+            V::template run<true>(p, s_pre, begin, end, w, ptot, arr, gr);
+    } else {
+        gr.locate(p, ptot);
+        for (int64_t x = begin; x < end;) {
+            const Segment s = locate(p, s_pre, x, end);
+            V::template segment<true>(p, s, x == begin ? 2 * w : 2 * w + 1, ptot, gr);
+            x = s.next;
+        }
+    }
+    V::combine_group(p, gl, arr);
+    if (p.combine == kCombineLast)
+        arr.template combine_last<D>(p, s_pre, ptot, gl.last);
+    else
+        arr.flush<true>(p);
+}
+
 }  // namespace
 
 typedef void (*kernel_fn)(AttnParams);
+
+// The group kernel and its LDS need beyond the prefix.
+kernel_fn verify_group_variant(int D, int NB, int *lds_bytes) {
+#define TS_VG(DD, NN)                                                \
+    if (D == DD && NB == NN) {                                       \
+        *lds_bytes = (int)sizeof(typename Verify<DD, NN>::GroupLds); \
+        return verify_group_kernel<DD, NN>;                          \
+    }
+    TS_VG(64, 1) TS_VG(64, 2) TS_VG(64, 3) TS_VG(64, 4) TS_VG(128, 1) TS_VG(128, 2)
+#undef TS_VG
+    return nullptr;
+}
 
 kernel_fn verify_variant(int D, int NB) {
 #define TS_VF(DD, NN) \
