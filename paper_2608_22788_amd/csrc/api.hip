@@ -428,12 +428,12 @@ int launch_attn(const ts_attn_shape *s, const void *q, const void *k_pages, cons
     p.B = s->num_seqs;
     p.Hq = s->num_q_heads;
     p.Hkv = s->num_kv_heads;
-    p.D = s->head_dim;
     p.Qmax = s->max_q_len;
     p.max_pages = s->max_pages_per_seq;
     p.G = pl.G;
     p.rows_per_unit = pl.rows_per_unit;
     p.W = pl.W;
+    p.range_inv = 0xffffffffu / (uint32_t)(pl.group ? kGroupWaves * pl.W : pl.W);
     p.ws_o_bytes = L.ws_o_bytes;
     p.combine = (int16_t)L.combine;
     p.cnt_shift = (int16_t)L.cnt_shift;

@@ -52,7 +52,8 @@ struct AttnParams {   // 128 bytes of kernel arguments
     float *ws_o;                // [2W][rows_per_unit][D] fp32 partial outputs
     float *ws_lse;              // [2W][rows_per_unit] fp32 log2-sum-exp
     int *counters;              // arrivals per split unit, unit u at u << cnt_shift (zero between calls)
-    int B, Hq, Hkv, D, Qmax, max_pages;
+    int B, Hq, Hkv, Qmax, max_pages;
+    uint32_t range_inv;         // floor((2^32 - 1) / ranges), ranges = W, or kGroupWaves W for groups
     int G;                      // Hq / Hkv
     int rows_per_unit;          // G * Qmax
     int W;                      // workers (wavefronts)
@@ -158,6 +159,21 @@ __device__ __forceinline__ int *unit_counter(const AttnParams &p, int unit) {
     return p.counters + ((size_t)unit << p.cnt_shift);
 }
 
+// x combined over the four lanes with the same lane % 16; each of them gets
+// the result.  Both operands of a swap are x, so it leaves rows {0, 0, 2, 2}
+// and {1, 1, 3, 3}, then halves {0, 0} and {1, 1} (vector-ALU moves, no LDS
+// round trip).
+template <typename F>
+__device__ __forceinline__ float across_lane_groups(float x, F f) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+__device__ __forceinline__ float max_across_lane_groups(float x) {
+    return across_lane_groups(x, [](float a, float b) { return fmaxf(a, b); });
+}
+
 // Metadata (page table, context and draft lengths) is read-only for the whole
 // launch.  Reading it through the constant address space lets wavefront-uniform
 // reads become scalar loads, which are counted separately from the vector
@@ -179,17 +195,43 @@ __device__ __forceinline__ int seq_pages(const AttnParams &p, int b) {
     return (Q > 0 && L > 0) ? (L + kPage - 1) / kPage : 0;
 }
 
+// Inclusive scan over a wavefront in vector-ALU lane moves (no LDS round
+// trips): four shifts inside each row of 16 lanes, then the last lane of a row
+// into the next row and the last lane of the lower half into the upper.
+template <int CTRL, int kRows>
+__device__ __forceinline__ int scan_step_i32(int x) {
+    return x + __builtin_amdgcn_update_dpp(0, x, CTRL, kRows, 0xf, false);
+}
+__device__ __forceinline__ int wave_incl_scan_i32(int x) {
+    x = scan_step_i32<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8
+    x = scan_step_i32<0x112, 0xf>(x);
+    x = scan_step_i32<0x114, 0xf>(x);
+    x = scan_step_i32<0x118, 0xf>(x);
+    x = scan_step_i32<0x142, 0xa>(x);   // row_bcast:15
+    return scan_step_i32<0x143, 0xc>(x);   // row_bcast:31
+}
+
 // Exclusive prefix of seq_pages into s_pre[0..B] (s_pre[B] = total), computed
 // by the first wavefront of the block; every thread must call it (it ends in
-// a block barrier).  Sequences are taken in batches of 64 * kPrefixRun: lane t
-// owns the run of kPrefixRun consecutive sequences starting at t * kPrefixRun.
+// a block barrier).  Up to 64 sequences take one lane each.  More are taken in
+// batches of 64 * kPrefixRun: lane t owns the run of kPrefixRun consecutive
+// sequences starting at t * kPrefixRun.
 // All lengths of a batch are loaded before any is used (one memory latency
 // for up to 512 sequences), the run totals are scanned across the wavefront
 // once, and each lane then writes its run's prefixes.
 constexpr int kPrefixRun = 8;
 
 __device__ inline void page_prefix(const AttnParams &p, int *s_pre) {
-    if (threadIdx.x < kWave) {
+    if (threadIdx.x < kWave && p.B <= kWave) {
+        const int lane = threadIdx.x;
+        const int v = seq_pages(p, min(lane, p.B - 1));
+        const int n = lane < p.B ? v : 0;
+        const int incl = wave_incl_scan_i32(n);
+        if (lane < p.B)
+            s_pre[lane] = incl - n;
+        if (lane == p.B - 1)
+            s_pre[p.B] = incl;
+    } else if (threadIdx.x < kWave) {
         const int lane = threadIdx.x;
         int base = 0;
         for (int b0 = 0; b0 < p.B; b0 += kPrefixRun * kWave) {
@@ -205,13 +247,7 @@ __device__ inline void page_prefix(const AttnParams &p, int *s_pre) {
                 n[k] = b < p.B ? v : 0;
                 run += n[k];
             }
-            int incl = run;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const int y = __shfl_up(incl, off, kWave);
-                if (lane >= off)
-                    incl += y;
-            }
+            const int incl = wave_incl_scan_i32(run);
             int acc = base + incl - run;
 #pragma unroll
             for (int k = 0; k < kPrefixRun; k++) {
@@ -219,7 +255,7 @@ __device__ inline void page_prefix(const AttnParams &p, int *s_pre) {
                     s_pre[first + k] = acc;
                 acc += n[k];
             }
-            base += __shfl(incl, kWave - 1, kWave);
+            base += __builtin_amdgcn_readlane(incl, kWave - 1);
         }
         if (lane == 0)
             s_pre[p.B] = base;
@@ -242,23 +278,38 @@ __device__ __forceinline__ int64_t worker_begin(int64_t ptot, int w, int W) {
     return (ptot * (int64_t)w) / (int64_t)W;
 }
 
+// The same for range w of `ranges`, p.range_inv being floor((2^32 - 1) /
+// ranges): in 32 bits the high word of the product with it is at most one
+// below the quotient, since it differs from the exact value by less than
+// x / 2^32 < 1.
+__device__ __forceinline__ int64_t range_begin(const AttnParams &p, int64_t ptot, int w, int ranges) {
+    const uint64_t x = (uint64_t)ptot * (uint32_t)w;
+    if (x >> 32)
+        return worker_begin(ptot, w, ranges);
+    const uint32_t q = __umulhi((uint32_t)x, p.range_inv);
+    return q + ((uint32_t)x - q * (uint32_t)ranges >= (uint32_t)ranges);
+}
+
 // Worker whose range holds global page x (0 <= x < ptot).
 __device__ __forceinline__ int worker_of(int64_t ptot, int64_t x, int W) {
     return (int)(((x + 1) * (int64_t)W - 1) / ptot);
 }
 
 // Sequence holding global page x: the largest b with Hkv * s_pre[b] <= x.
+// Called by whole wavefronts: the lanes compare every step-th sequence, then
+// those of the step found (two LDS round trips for any number of sequences).
 __device__ __forceinline__ int find_seq(const int *s_pre, int B, int64_t x, int Hkv) {
-    const int64_t y = x / Hkv;
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if ((int64_t)s_pre[mid] <= y)
-            lo = mid;
-        else
-            hi = mid - 1;
+    static_assert(kMaxSeqs <= kWave * kWave, "two levels of 64");
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = 0, n = B;
+    if (B > kWave) {
+        const int step = (B + kWave - 1) / kWave;
+        const int at = lane * step;
+        lo = step * (__popcll(__ballot(at < B && (int64_t)Hkv * s_pre[min(at, B)] <= x)) - 1);
+        n = min(step, B - lo);
     }
-    return lo;
+    const int at = lo + min(lane, n);
+    return lo + __popcll(__ballot(lane < n && (int64_t)Hkv * s_pre[at] <= x)) - 1;
 }
 
 struct Segment {
@@ -278,8 +329,9 @@ __device__ __forceinline__ Segment locate(const AttnParams &p, const int *s_pre,
     const int np = first_lane_int(s_pre[s.b + 1]) - first;
     const int64_t base = (int64_t)p.Hkv * first;
     const int64_t off = x - base;
-    s.g = first_lane_int((int)(off / np));
-    s.j0 = first_lane_int((int)(off % np));
+    const int64_t unit = off / np;
+    s.g = first_lane_int((int)unit);
+    s.j0 = first_lane_int((int)(off - unit * np));
     const int64_t unit_end = base + (int64_t)(s.g + 1) * np;
     const int64_t seg_end = unit_end < range_end ? unit_end : range_end;
     s.j1 = first_lane_int(s.j0 + (int)(seg_end - x));

@@ -325,8 +325,8 @@ __global__ __launch_bounds__(64) void decode_q1_kernel(AttnParams p) {
     }
     const int64_t ptot = (int64_t)p.Hkv * s_pre[p.B];
     const int w = xcd_worker(blockIdx.x, p.W);
-    const int64_t begin = worker_begin(ptot, w, p.W);
-    const int64_t end = worker_begin(ptot, w + 1, p.W);
+    const int64_t begin = range_begin(p, ptot, w, p.W);
+    const int64_t end = range_begin(p, ptot, w + 1, p.W);
     Arrivals arr;
     arr.init();
     for (int64_t x = begin; x < end;) {

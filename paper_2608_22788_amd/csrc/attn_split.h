@@ -138,6 +138,31 @@ struct Acc {
                     v[k][e] = *reinterpret_cast<const float4 *>(src + 4 * e);
             }
         }
+        add_loaded<kB>(l, v);
+    }
+    // Adds the first n (of up to kB) partials at rows at[0 .. n - 1] of the
+    // partial area, with device-coherent loads.
+    template <int D, int kB>
+    __device__ void add_at(const AttnParams &p, const uint32_t *at, int n, int part) {
+        float l[kB];
+        float4 v[kB][VE / 4];
+#pragma unroll
+        for (int k = 0; k < kB; k++) {
+            l[k] = ld_coherent(p.ws_lse + at[k]);
+#pragma unroll
+            for (int e = 0; e < VE / 4; e++) {
+                const f32x4_t t = ld_partial16(p, (size_t)(at[k] * (uint32_t)D + (uint32_t)(VE * part + 4 * e)));
+                v[k][e] = make_float4(t[0], t[1], t[2], t[3]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kB; k++)
+            l[k] = k < n ? l[k] : -INFINITY;
+        add_loaded<kB>(l, v);
+    }
+    // Adds kB partials held in registers (those with l = -inf count nothing).
+    template <int kB>
+    __device__ void add_loaded(const float (&l)[kB], const float4 (&v)[kB][VE / 4]) {
         float Mb = M;
 #pragma unroll
         for (int k = 0; k < kB; k++)
@@ -403,19 +428,10 @@ __device__ __forceinline__ bool wait_count(const int *c, int target) {
 
 // Sums of the four 16-lane groups (same part, different pieces) combined;
 // every group gets the total.
-template <typename F>
-__device__ __forceinline__ float across_lane_groups(float x, F f) {
-    // both operands x: the swap leaves rows {0, 0, 2, 2} and {1, 1, 3, 3},
-    // then halves {0, 0} and {1, 1} (vector-ALU moves, no LDS round trip)
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
-}
 template <int VE>
 __device__ __forceinline__ void combine_lane_groups(Acc<VE> &a) {
     const auto add = [](float x, float y) { return x + y; };
-    const float Mall = across_lane_groups(a.M, [](float x, float y) { return fmaxf(x, y); });
+    const float Mall = max_across_lane_groups(a.M);
     const float f = a.M == -INFINITY ? 0.0f : fast_exp2(a.M - Mall);
     a.den = across_lane_groups(a.den * f, add);
 #pragma unroll
@@ -441,10 +457,26 @@ __device__ void merge_in_launch(const AttnParams &p, const int *s_pre, int unit,
         return;   // one worker saw the whole unit and wrote `out`
     const int lane = threadIdx.x & 63;
     int *cnt = unit_counter(p, unit);
+    // Up to 4 * kMergeBatch pieces: where they lie is worked out before the
+    // wait, so that only the loads follow it.
+    constexpr int VE = D / 16;
+    uint32_t at[kMergeBatch];
+#pragma unroll
+    for (int k = 0; k < kMergeBatch; k++) {
+        const int kk = (lane >> 4) + 4 * k;
+        at[k] = (uint32_t)u.slot(kk < u.nparts ? kk : 0) * (uint32_t)p.rows_per_unit + (uint32_t)r;
+    }
+    const int nmine = (u.nparts - (lane >> 4) + 3) >> 2;   // this lane group's pieces
     const bool ok = wait_count(cnt, u.nparts);
-    Acc<D / 16> a;
+    Acc<VE> a;
     a.init();
-    if (ok) {
+    if (ok && u.nparts <= 4 * kMergeBatch) {
+        // 16 pieces and fewer take half of the loads (wavefront-uniform)
+        if (u.nparts <= 2 * kMergeBatch)
+            a.template add_at<D, kMergeBatch / 2>(p, at, nmine, lane & 15);
+        else
+            a.template add_at<D, kMergeBatch>(p, at, nmine, lane & 15);
+    } else if (ok) {
         gather_partials<D, true>(p, u, r, lane & 15, lane >> 4, 4, a);
     } else {
 #pragma unroll

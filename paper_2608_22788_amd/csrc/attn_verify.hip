@@ -154,18 +154,22 @@ struct Verify {
             float mx = fmaxf(fmaxf(ok[0] ? x[0] : -INFINITY, ok[1] ? x[1] : -INFINITY),
                              fmaxf(ok[2] ? x[2] : -INFINITY, ok[3] ? x[3] : -INFINITY));
             if (__any(mx > st.m_ref[rb] + kRescaleSlack)) {
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                mx = max_across_lane_groups(mx);
                 const bool up = mx > st.m_ref[rb] + kRescaleSlack;
                 const float alpha = up ? fast_exp2(st.m_ref[rb] - mx) : 1.0f;
+                // rows without a reference have no sums to scale: nothing to
+                // do on a segment's first page
+                const bool sums = __any(up && st.m_ref[rb] != -INFINITY);
                 st.m_ref[rb] = up ? mx : st.m_ref[rb];
+                if (sums) {
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const float ai = __shfl(alpha, 4 * kq + i);
-                    st.lacc[rb][i] *= ai;
+                    for (int i = 0; i < 4; i++) {
+                        const float ai = __shfl(alpha, 4 * kq + i);
+                        st.lacc[rb][i] *= ai;
 #pragma unroll
-                    for (int jj = 0; jj < VE; jj++)
-                        st.acc[rb][jj][i] *= ai;
+                        for (int jj = 0; jj < VE; jj++)
+                            st.acc[rb][jj][i] *= ai;
+                    }
                 }
             }
             const float p0 = ok[0] ? fast_exp2(x[0] - st.m_ref[rb]) : 0.0f;
@@ -254,8 +258,9 @@ struct Verify {
         int wg;              // the group's worker index
         int64_t begin, end;  // its global pages
         __device__ void locate(const AttnParams &p, int64_t ptot) {
-            begin = first_lane_int64(worker_begin(ptot, wg, p.W));
-            end = first_lane_int64(worker_begin(ptot, wg + 1, p.W));
+            const int ranges = kGroupWaves * p.W;
+            begin = first_lane_int64(range_begin(p, ptot, kGroupWaves * wg, ranges));
+            end = first_lane_int64(range_begin(p, ptot, kGroupWaves * (wg + 1), ranges));
         }
     };
 
@@ -577,8 +582,8 @@ __global__ __launch_bounds__(64) void verify_kernel(AttnParams p) {
     }
     const int64_t ptot = (int64_t)p.Hkv * first_lane_int(s_pre[p.B]);
     const int w = xcd_worker(blockIdx.x, p.W);
-    const int64_t begin = worker_begin(ptot, w, p.W);
-    const int64_t end = worker_begin(ptot, w + 1, p.W);
+    const int64_t begin = range_begin(p, ptot, w, p.W);
+    const int64_t end = range_begin(p, ptot, w + 1, p.W);
     Arrivals arr;
     arr.init();
     if constexpr (NB == 1) {
@@ -621,8 +626,8 @@ __global__ __launch_bounds__(kGroupWaves * kWave, NB == 1 ? 2 : 1) void verify_g
         gl.rec[2 * wave + (threadIdx.x & (kWave - 1))].unit = -1;
     const int64_t ptot = (int64_t)p.Hkv * first_lane_int(s_pre[p.B]);
     const int wg = xcd_worker(blockIdx.x, p.W), w = kGroupWaves * wg + wave;
-    const int64_t begin = first_lane_int64(worker_begin(ptot, w, kGroupWaves * p.W));
-    const int64_t end = first_lane_int64(worker_begin(ptot, w + 1, kGroupWaves * p.W));
+    const int64_t begin = first_lane_int64(range_begin(p, ptot, w, kGroupWaves * p.W));
+    const int64_t end = first_lane_int64(range_begin(p, ptot, w + 1, kGroupWaves * p.W));
     typename V::Group gr{&gl, wg, 0, 0};
     Arrivals arr;
     arr.init();

@@ -216,18 +216,22 @@ struct Team {
         // reference by more than the slack, which is rare after the first page.
         float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
         if (__any(mx > st.m_ref + kRescaleSlack)) {
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = max_across_lane_groups(mx);
             const bool up = mx > st.m_ref + kRescaleSlack;
             const float alpha = up ? fast_exp2(st.m_ref - mx) : 1.0f;
+            // rows without a reference have no sums to scale: nothing to do on
+            // a segment's first page
+            const bool sums = __any(up && st.m_ref != -INFINITY);
             st.m_ref = up ? mx : st.m_ref;
+            if (sums) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const float ai = __shfl(alpha, 4 * kq + i);
-                st.lacc[i] *= ai;
+                for (int i = 0; i < 4; i++) {
+                    const float ai = __shfl(alpha, 4 * kq + i);
+                    st.lacc[i] *= ai;
 #pragma unroll
-                for (int jj = 0; jj < 8; jj++)
-                    st.acc[jj][i] *= ai;
+                    for (int jj = 0; jj < 8; jj++)
+                        st.acc[jj][i] *= ai;
+                }
             }
         }
         float pr[4];
@@ -446,8 +450,8 @@ __global__ __launch_bounds__(256) void verify_team_kernel(AttnParams p) {
     }
     const int64_t ptot = (int64_t)p.Hkv * s_pre[p.B];
     const int w = xcd_worker(blockIdx.x, p.W);
-    const int64_t begin = worker_begin(ptot, w, p.W);
-    const int64_t end = worker_begin(ptot, w + 1, p.W);
+    const int64_t begin = range_begin(p, ptot, w, p.W);
+    const int64_t end = range_begin(p, ptot, w + 1, p.W);
     Arrivals arr;
     arr.init();
     for (int64_t x = begin; x < end;) {

@@ -103,9 +103,9 @@ __global__ __launch_bounds__(kWave) void page_gather_kernel(AttnParams p, uint32
     const int lane = threadIdx.x;
     const int64_t ptot = (int64_t)p.Hkv * s_pre[p.B];
     const int w = xcd_worker(blockIdx.x, p.W);
-    const int64_t end = worker_begin(ptot, w + 1, p.W);
+    const int64_t end = range_begin(p, ptot, w + 1, p.W);
     uint32_t acc = 0;
-    for (int64_t x = worker_begin(ptot, w, p.W); x < end;) {
+    for (int64_t x = range_begin(p, ptot, w, p.W); x < end;) {
         const Segment s = locate(p, s_pre, x, end);
         const int32_t *pt = p.page_table + (size_t)s.b * p.max_pages;
         GatherPage<D> r0, r1;
@@ -203,11 +203,11 @@ int ts_page_gather_read(const ts_attn_shape *s, const void *k_pages, const void 
     p.B = s->num_seqs;
     p.Hq = s->num_q_heads;
     p.Hkv = s->num_kv_heads;
-    p.D = s->head_dim;
     p.Qmax = s->max_q_len;
     p.max_pages = s->max_pages_per_seq;
     p.W = W;
-    void (*k)(AttnParams, uint32_t *) = p.D == 64 ? page_gather_kernel<64> : page_gather_kernel<128>;
+    p.range_inv = 0xffffffffu / (uint32_t)W;
+    void (*k)(AttnParams, uint32_t *) = s->head_dim == 64 ? page_gather_kernel<64> : page_gather_kernel<128>;
     uint32_t *out = static_cast<uint32_t *>(sink);
     void *args[] = {&p, &out};
     hipError_t e = hipExtLaunchKernel(reinterpret_cast<const void *>(k), dim3(W), dim3(kWave), args,
