@@ -42,7 +42,7 @@ TRAFFIC_SOURCES = {
     "mtp": ["csrc/attn_common.h", "csrc/attn_split.h", "csrc/attn_verify.hip", "csrc/api.hip", "build.py"],
     "dflash": ["csrc/attn_common.h", "csrc/attn_split.h", "csrc/attn_verify_team.hip", "csrc/api.hip", "build.py"],
 }
-KERNELS = {"bulk": "verify_kernel<128,1>", "mtp": "verify_kernel<128,1>",
+KERNELS = {"bulk": "verify_group_kernel<128,1>", "mtp": "verify_group_kernel<128,1>",
            "dflash": "verify_team_kernel<4>"}
 
 WORKLOADS = {
@@ -249,7 +249,10 @@ PLAN_COMBINE = {0: "merge kernel after the launch", 1: "last arriver in the laun
 def plan_summary(plan):
     """What the timed call launched (ts_decode_attn_plan): kernel, workers,
     how its splits were combined, workgroups of the streaming launch."""
-    return dict(kernel=PLAN_KERNEL.get(plan["variant"], str(plan["variant"])), workers=plan["num_workers"],
+    kernel = PLAN_KERNEL.get(plan["variant"], str(plan["variant"]))
+    if plan["variant"] == 1 and plan.get("threads") == 256:
+        kernel += ", four wavefronts a worker"
+    return dict(kernel=kernel, workers=plan["num_workers"],
                 combine=PLAN_COMBINE.get(plan["combine"], str(plan["combine"])), grid=plan["grid"])
 
 

@@ -82,14 +82,17 @@ typedef enum ts_status {
  * max_q_len in 1..16; num_seqs in 1..4096; num_seqs * num_kv_heads <= 2^18.
  * max_ctx_len is an upper bound on ctx_lens, used for validation and to size
  * the automatic worker count; the launch grid depends on the shape alone.
- * num_workers = 0 lets the library choose how many workers (one wavefront,
- * or a four-wavefront team for verify at head_dim 128) share the KV stream;
+ * num_workers = 0 lets the library choose how many workers (four wavefronts
+ * each with TS_VARIANT_AUTO, else one wavefront or a four-wavefront team)
+ * share the KV stream;
  * a positive value fixes it (the result does not depend on it
  * beyond rounding; tests use it to vary the split points).  variant selects
  * the kernel:
  *   TS_VARIANT_AUTO  the matrix-core kernel in which one wavefront holds
  *                    every row block for up to 32 rows per (sequence, KV
- *                    head), the team kernel beyond (head_dim 128);
+ *                    head), its wavefronts grouped four to a worker unless
+ *                    num_workers is given; the team kernel beyond (head_dim
+ *                    128);
  *   TS_VARIANT_WAVE  the single-wavefront matrix-core kernel, any shape;
  *   TS_VARIANT_TEAM  head_dim 128 only: four wavefronts share each page
  *                    through LDS;

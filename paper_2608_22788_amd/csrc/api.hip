@@ -100,18 +100,6 @@ static int per_cu_bound(bool q1, bool team, int rows) {
     return rows <= 8 ? 4 : 3;
 }
 
-// Workers (workgroups of four wavefronts) of the group kernel: one per compute
-// unit, and no more than four pages' worth of the upper bound on the work (a
-// page per wavefront).  Two per compute unit stream slower (32 sequences,
-// q_len 1: 88.0 against 83.3 us; 4 with q_len 4: 24.8 against 22.0); eight
-// pages per worker lengthen the chain of the smallest calls (one sequence of
-// 1,600 tokens: 11.8 against 10.7 us).
-static int group_workers(const ts_attn_shape *s) {
-    const int64_t pages_ub = (int64_t)s->num_seqs * s->num_kv_heads *
-                             ((s->max_ctx_len + kPage - 1) / kPage);
-    return (int)std::min<int64_t>(256, (pages_ub + kGroupWaves - 1) / kGroupWaves);
-}
-
 static int auto_workers(const ts_attn_shape *s, bool q1, bool team, int rows) {
     int64_t w = 256LL * per_cu_bound(q1, team, rows);
     // Small shapes get fewer workers so that each has at least a few pages.
@@ -137,6 +125,22 @@ static int auto_workers(const ts_attn_shape *s, bool q1, bool team, int rows) {
     if (w > 256)
         w -= w % 256;
     return (int)(w < 1 ? 1 : w);
+}
+
+// Workers (workgroups of four wavefronts) of the group kernel: one per compute
+// unit, and no more than four pages' worth of the upper bound on the work (a
+// page per wavefront).  Two per compute unit stream slower (32 sequences,
+// q_len 1: 88.0 against 83.3 us; 4 with q_len 4: 24.8 against 22.0); eight
+// pages per worker lengthen the chain of the smallest calls (one sequence of
+// 1,600 tokens: 11.8 against 10.7 us).  Nor more than single wavefronts would
+// be, which bounds the pieces of a call with very few units (4 units of 1,300
+// tokens: 11.5 us with 15 pieces each, 12.0 with 30) and keeps every workspace
+// that was large enough for them large enough.
+static int group_workers(const ts_attn_shape *s, int rows) {
+    const int64_t pages_ub = (int64_t)s->num_seqs * s->num_kv_heads *
+                             ((s->max_ctx_len + kPage - 1) / kPage);
+    return (int)std::min<int64_t>({256, (pages_ub + kGroupWaves - 1) / kGroupWaves,
+                                   auto_workers(s, false, false, rows)});
 }
 
 // Workgroups of `k` resident per compute unit times the compute units, or 0
@@ -240,7 +244,7 @@ int make_plan(const ts_attn_shape *s, Plan *pl) {
     if (s->num_workers > 0)
         pl->W = s->num_workers;
     else
-        pl->W = pl->group ? group_workers(s) : auto_workers(s, pl->q1, pl->team, pl->rows_per_unit);
+        pl->W = pl->group ? group_workers(s, pl->rows_per_unit) : auto_workers(s, pl->q1, pl->team, pl->rows_per_unit);
     // Workspace: the split counters first, at a fixed size whatever the shape,
     // so that no call's partial results ever land on them (they are zero
     // between calls); then 256 bytes for the TS_DEBUG check's flag word; then

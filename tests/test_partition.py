@@ -29,3 +29,17 @@ def test_range_begin_at_the_top_of_its_range():
         top = 0xFFFFFFFF // w
         ptot = top - rng.randrange(min(top, 3) + 1)
         assert range_begin(ptot, w, ranges) == ptot * w // ranges
+
+
+def test_groups_need_no_larger_workspace_than_single_wavefronts():
+    """The automatic kernel choice fits every workspace that was sized for
+    single-wavefront workers (TS_VARIANT_WAVE)."""
+    from paper_2608_22788_amd import binding
+    for B in (1, 2, 3, 8, 40, 300):
+        for hkv in (1, 2, 8):
+            for ctx in (1, 16, 17, 100, 181, 700, 1878, 4000, 60000):
+                for G, Q, D in ((1, 1, 64), (4, 1, 128), (4, 4, 128), (8, 4, 128), (4, 12, 64), (4, 16, 64)):
+                    maxp = (ctx + 15) // 16
+                    size = [binding.workspace_size(binding.make_shape(B, G * hkv, hkv, D, Q, maxp, ctx, B * maxp, 0, 16, v))
+                            for v in (0, 1)]
+                    assert 0 < size[0] <= size[1], (B, hkv, ctx, G, Q, D, size)
