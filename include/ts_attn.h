@@ -43,7 +43,9 @@
  * call leaves the counters zero again and never writes anything else over
  * them, so a workspace can be reused by any later call, of any shape, on one
  * stream (the rest of its contents is undefined on return).  Calls that may
- * run concurrently need distinct workspaces.  Every entry point
+ * run concurrently need distinct workspaces; no two such calls can hold each
+ * other up (a call whose merge workgroups wait for its workers fills at most
+ * half of the device with them).  Every entry point
  * returns TS_OK (0) or a negative ts_status; on error nothing is launched and
  * ts_last_error() describes the cause.  No C++ exception crosses the ABI.
  *

@@ -321,7 +321,7 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
     //    pieces);
     //  * merge wavefronts appended to the grid, one per row of each unit, when
     //    units have many pieces (a unit meets about W / units + 1 workers;
-    //    here W >= 8 units) and that takes at most kMaxMergeWgs workgroups;
+    //    here W >= 8 units) and that takes at most max_merge_wgs workgroups;
     //  * otherwise the merge kernel after the launch, and always when the
     //    partial area is too large for 32-bit buffer offsets.
     // Measured against the merge kernel (per call; 32/8 heads, head_dim 128):
@@ -333,24 +333,42 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
     // A group's merge workgroup takes four rows and a group leaves fewer
     // pieces, so for groups the workgroup count alone decides: at 128-256
     // merge workgroups (4-8 sequences with q_len 4) it is 1.2-1.5 us faster
-    // than the merge kernel, at 448 0.8 us, at 640 1.9 us slower.  Two such
-    // workgroups fit on a compute unit, so with at most 256 of them one call
-    // never holds every slot of an XCD with wavefronts that wait.  Past that,
+    // than the merge kernel, at 448 0.8 us, at 640 1.9 us slower.  Past that,
     // from two units a worker the last arriver combines (256 sequences with
     // 32 rows: 297.9 against 299.9 us with the merge kernel); at one unit a
     // worker it was 3-7 % slower than the merge kernel.
-    const int64_t kMaxMergeWgs = pl.group ? 256 : 512;
+    // Whatever the kernel, the merge workgroups, which hold their slots while
+    // they wait, may fill at most half of the device's (attn_split.h, forward
+    // progress).  A slot is as large as a worker's: one per compute unit for
+    // groups of two and more row blocks (of three at head_dim 64), two for
+    // the others and for teams.  That leaves the block-draft workload, with
+    // 512 merge workgroups of teams, to the merge kernel: 170.0 against 168.5
+    // us per call.
+    size_t lds = L.main_lds;
+    if (pl.team && pl.auto_w) {
+        // In that mode, reserve enough LDS that only the workers' teams fit on
+        // a compute unit (their registers would allow one more): a merge
+        // workgroup then starts where a team has finished instead of polling
+        // beside two streaming teams from the start, which measured 1 % faster.
+        const size_t lds_cu = (size_t)160 * 1024;
+        const int teams = per_cu_bound(false, true, pl.rows_per_unit);
+        lds = std::max(lds, ((lds_cu / teams + lds_cu / (teams + 1)) / 2) & ~(size_t)1023);
+    }
+    const int64_t max_merge_wgs =
+        std::min<int64_t>(pl.group ? 256 : 512, resident_workers(L.main_k, L.main_threads, lds) / 2);
     const size_t o_bytes = pl.ws_lse_off - pl.ws_o_off;
     const int64_t units = (int64_t)B * Hkv;
     const int ngroups = (pl.rows_per_unit + 3) / 4;
     const int64_t merge_wgs = units * (pl.team || pl.group ? ngroups : pl.rows_per_unit);
     L.combine = kCombineKernel;
     if (o_bytes < ((size_t)1 << 31)) {
-        if ((pl.group || (int64_t)pl.W >= 8 * units) && merge_wgs <= kMaxMergeWgs)
+        if ((pl.group || (int64_t)pl.W >= 8 * units) && merge_wgs <= max_merge_wgs)
             L.combine = kCombineInLaunch;
         else if (!pl.team && units >= 2 * (int64_t)pl.W)
             L.combine = kCombineLast;
     }
+    if (L.combine == kCombineInLaunch)
+        L.main_lds = lds;
     L.ws_o_bytes = L.combine != kCombineKernel ? (int)o_bytes : 0;
     // Counters of consecutive units up to 4 KiB apart (inside the counter
     // area) when merge wavefronts poll them.
@@ -359,17 +377,6 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
         while (L.cnt_shift < 10 && units << (L.cnt_shift + 1) <= kMaxUnits)
             L.cnt_shift++;
     L.grid = (unsigned)(pl.W + (L.combine == kCombineInLaunch ? merge_wgs : 0));
-    if (L.combine == kCombineInLaunch && pl.team && pl.auto_w) {
-        // Reserve enough LDS that only the workers' teams fit on a compute
-        // unit (their registers would allow one more): a merge workgroup then
-        // starts where a team has finished instead of polling beside two
-        // streaming teams from the start, which measured 1 % faster.
-        const size_t lds_cu = (size_t)160 * 1024;
-        const int teams = per_cu_bound(false, true, pl.rows_per_unit);
-        const size_t gate = ((lds_cu / teams + lds_cu / (teams + 1)) / 2) & ~(size_t)1023;
-        if (L.main_lds < gate)
-            L.main_lds = gate;
-    }
     if (L.combine == kCombineKernel) {
         // A unit meets about W / units + 1 workers.  Up to about three pieces
         // a unit, one wavefront per 4 rows takes every piece itself (a fourth

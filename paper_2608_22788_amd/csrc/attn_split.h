@@ -398,11 +398,16 @@ __device__ void combine_waves(Acc<VE> &a, float *comb, int wave, int lane) {
 // whole grid was a large share of a short call.
 //
 // Forward progress: the dispatcher starts the workgroups of each XCD in
-// increasing order, so every worker has started before any merge workgroup
-// of its XCD, and workers never wait.  A merge wavefront therefore only
-// waits for workgroups that are running.  The wait is bounded all the same
-// (kMergeSpins polls); a wavefront that gives up writes NaN, so such a
-// failure shows in the output instead of as a hang.
+// increasing order, so the merge workgroups of an XCD start after the workers
+// of that XCD, and workers never wait.  But the workers of the other XCDs need
+// not have started: another call, on another stream, may hold the slots they
+// need with merge workgroups of its own.  The host therefore takes this mode
+// only while the merge workgroups fill at most half of the slots of every XCD.
+// Of two overlapping calls at least one then finds room for its workers beside
+// the other's merge workgroups on every XCD, finishes, and frees the other.
+// (Three calls and more can fill an XCD between them.)  The wait is bounded
+// all the same (kMergeSpins polls); a wavefront that gives up writes NaN, so
+// such a failure shows in the output instead of as a hang.
 //
 // Counter protocol: the unit's counter reaches nparts once every worker has
 // arrived; then each merge wavefront of the unit with a valid row adds one
