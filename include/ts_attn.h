@@ -43,9 +43,12 @@
  * call leaves the counters zero again and never writes anything else over
  * them, so a workspace can be reused by any later call, of any shape, on one
  * stream (the rest of its contents is undefined on return).  Calls that may
- * run concurrently need distinct workspaces; no two such calls can hold each
- * other up (a call whose merge workgroups wait for its workers fills at most
- * half of the device with them).  Every entry point
+ * run concurrently need distinct workspaces; any number of them finishes, with
+ * the results that each gives alone.  (A call whose merge workgroups wait for
+ * its workers fills at most half of the device with them, so two such calls
+ * never hold each other up; of three and more, one may wait some milliseconds
+ * until the others' merge workgroups give up and leave their rows to the
+ * workers.)  Every entry point
  * returns TS_OK (0) or a negative ts_status; on error nothing is launched and
  * ts_last_error() describes the cause.  No C++ exception crosses the ABI.
  *
@@ -147,6 +150,16 @@ int ts_decode_attn_events(const ts_attn_shape *shape, const void *q, const void 
                           const int32_t *ctx_lens, const int32_t *q_lens, void *out,
                           float scale, void *workspace, size_t workspace_bytes, void *stream,
                           void *ev_begin, void *ev_end);
+
+/* ts_decode_attn whose merge wavefronts (TS_COMBINE_IN_LAUNCH below) give up
+ * after merge_polls (0..32767) polls of their unit's counter and leave the row
+ * to the worker that arrives last: for tests of that hand-over.  The result
+ * does not depend on it. */
+int ts_decode_attn_polls(const ts_attn_shape *shape, const void *q, const void *k_pages,
+                         const void *v_pages, const int32_t *page_table,
+                         const int32_t *ctx_lens, const int32_t *q_lens, void *out,
+                         float scale, void *workspace, size_t workspace_bytes, void *stream,
+                         int32_t merge_polls);
 
 /* What ts_decode_attn launches for `shape` on the current device, for
  * diagnostics and tests: nothing is launched and no device memory is read.

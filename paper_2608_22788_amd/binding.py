@@ -66,7 +66,7 @@ class SweepPoint(ctypes.Structure):
 
 
 EXPORTS = ["ts_decode_attn_workspace_size", "ts_decode_attn", "ts_decode_attn_events", "ts_decode_attn_noalloc",
-           "ts_decode_attn_plan",
+           "ts_decode_attn_polls", "ts_decode_attn_plan",
            "ts_concurrency_sweep", "ts_synth_fill_bf16", "ts_synth_sweep_lengths",
            "ts_synth_page_table", "ts_copy_bytes", "ts_stream_read", "ts_page_gather_read", "ts_event_create", "ts_event_destroy",
            "ts_event_record", "ts_event_elapsed_ms", "ts_status_string", "ts_last_error",
@@ -94,6 +94,8 @@ def _load() -> ctypes.CDLL:
     lib.ts_decode_attn.restype = ctypes.c_int
     lib.ts_decode_attn_events.argtypes = attn_args + [P, P]
     lib.ts_decode_attn_events.restype = ctypes.c_int
+    lib.ts_decode_attn_polls.argtypes = attn_args + [I32]
+    lib.ts_decode_attn_polls.restype = ctypes.c_int
     lib.ts_concurrency_sweep.argtypes = [ctypes.POINTER(SweepConfig), ctypes.POINTER(SweepPoint),
                                          I32, ctypes.POINTER(I32)]
     lib.ts_concurrency_sweep.restype = ctypes.c_int

@@ -394,7 +394,7 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
 int launch_attn(const ts_attn_shape *s, const void *q, const void *k_pages, const void *v_pages,
                   const int32_t *page_table, const int32_t *ctx_lens, const int32_t *q_lens,
                   void *out, float scale, void *workspace, size_t workspace_bytes, void *stream,
-                  void *ev_begin, void *ev_end) {
+                  void *ev_begin, void *ev_end, int merge_polls) {
     clear_error();
     Plan pl;
     int st = make_plan(s, &pl);
@@ -411,6 +411,8 @@ int launch_attn(const ts_attn_shape *s, const void *q, const void *k_pages, cons
         return fail(TS_ERR_ARG, "misaligned pointer (workspace needs 256 B, tensors 16 B)");
     if (!std::isfinite(scale))
         return fail(TS_ERR_ARG, "scale is not finite");
+    if (merge_polls < 0 || merge_polls > INT16_MAX)
+        return fail(TS_ERR_ARG, "merge_polls %d outside [0, %d]", merge_polls, INT16_MAX);
     Launch L;
     st = finish_plan(s, pl, L);
     if (st)
@@ -446,8 +448,9 @@ int launch_attn(const ts_attn_shape *s, const void *q, const void *k_pages, cons
     p.W = pl.W;
     p.range_inv = 0xffffffffu / (uint32_t)(pl.group ? kGroupWaves * pl.W : pl.W);
     p.ws_o_bytes = L.ws_o_bytes;
-    p.combine = (int16_t)L.combine;
-    p.cnt_shift = (int16_t)L.cnt_shift;
+    p.combine = (int8_t)L.combine;
+    p.cnt_shift = (int8_t)L.cnt_shift;
+    p.merge_polls = (int16_t)merge_polls;
     p.scale_log2 = scale * 1.4426950408889634f;
 
     hipError_t e;
@@ -521,7 +524,7 @@ int ts_decode_attn(const ts_attn_shape *shape, const void *q, const void *k_page
                    size_t workspace_bytes, void *stream) {
     try {
         return launch_attn(shape, q, k_pages, v_pages, page_table, ctx_lens, q_lens, out, scale,
-                      workspace, workspace_bytes, stream, nullptr, nullptr);
+                      workspace, workspace_bytes, stream, nullptr, nullptr, kMergePolls);
     } catch (...) {
         return fail(TS_ERR_HIP, "unexpected C++ exception");
     }
@@ -534,7 +537,20 @@ int ts_decode_attn_events(const ts_attn_shape *shape, const void *q, const void 
                           void *ev_begin, void *ev_end) {
     try {
         return launch_attn(shape, q, k_pages, v_pages, page_table, ctx_lens, q_lens, out, scale,
-                      workspace, workspace_bytes, stream, ev_begin, ev_end);
+                      workspace, workspace_bytes, stream, ev_begin, ev_end, kMergePolls);
+    } catch (...) {
+        return fail(TS_ERR_HIP, "unexpected C++ exception");
+    }
+}
+
+int ts_decode_attn_polls(const ts_attn_shape *shape, const void *q, const void *k_pages,
+                         const void *v_pages, const int32_t *page_table,
+                         const int32_t *ctx_lens, const int32_t *q_lens, void *out,
+                         float scale, void *workspace, size_t workspace_bytes, void *stream,
+                         int32_t merge_polls) {
+    try {
+        return launch_attn(shape, q, k_pages, v_pages, page_table, ctx_lens, q_lens, out, scale,
+                      workspace, workspace_bytes, stream, nullptr, nullptr, merge_polls);
     } catch (...) {
         return fail(TS_ERR_HIP, "unexpected C++ exception");
     }

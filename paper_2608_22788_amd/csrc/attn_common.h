@@ -41,6 +41,11 @@ constexpr int kCombineKernel = 0;    // a separate merge kernel (plain stores)
 constexpr int kCombineLast = 1;      // the last worker to finish a piece of the unit
 constexpr int kCombineInLaunch = 2;  // merge workgroups after the W workers of the grid
 
+// Polls after which a merge wavefront gives up (attn_split.h): about 6 ms,
+// longer than any call over less than 40 GB of K/V takes, and short enough for
+// a hold-up that only three overlapping calls can cause.
+constexpr int kMergePolls = 8192;
+
 struct AttnParams {   // 128 bytes of kernel arguments
     const uint16_t *q;          // [B][Qmax][Hq][D] bf16
     const uint16_t *k_pages;    // [num_pages][Hkv][P][D] bf16
@@ -58,8 +63,9 @@ struct AttnParams {   // 128 bytes of kernel arguments
     int rows_per_unit;          // G * Qmax
     int W;                      // workers (wavefronts)
     int ws_o_bytes;             // bytes of the partial area (set unless kCombineKernel; < 2^31)
-    int16_t combine;            // kCombine*: who combines the split partials
-    int16_t cnt_shift;          // log2 of the ints between the counters of consecutive units
+    int8_t combine;             // kCombine*: who combines the split partials
+    int8_t cnt_shift;           // log2 of the ints between the counters of consecutive units
+    int16_t merge_polls;        // polls a merge wavefront waits before it leaves its row to the last worker
     float scale_log2;           // scale * log2(e)
 };
 

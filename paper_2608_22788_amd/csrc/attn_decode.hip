@@ -335,7 +335,7 @@ __global__ __launch_bounds__(64) void decode_q1_kernel(AttnParams p) {
         arr.add(p, s);
         x = s.next;
     }
-    arr.flush<false>(p);
+    arr.template flush<D, false>(p, s_pre, ptot);
 }
 
 }  // namespace

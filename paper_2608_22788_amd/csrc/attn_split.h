@@ -170,6 +170,11 @@ struct Acc {
         if (Mb == -INFINITY)
             return;
         rescale(Mb);
+        add_weighted<kB>(l, v);
+    }
+    // The same with M at least their maximum already.
+    template <int kB>
+    __device__ void add_weighted(const float (&l)[kB], const float4 (&v)[kB][VE / 4]) {
 #pragma unroll
         for (int k = 0; k < kB; k++) {
             const float wt = l[k] == -INFINITY ? 0.0f : fast_exp2(l[k] - M);
@@ -332,20 +337,10 @@ struct Arrivals {
         const int np = s_pre[b + 1] - s_pre[b];
         return unit_split(ptot, (int64_t)p.Hkv * s_pre[b] + (int64_t)g * np, np, p.W);
     }
-    // Called by every thread of the workgroup; the first thread counts.
-    template <bool kBlock>
-    __device__ __forceinline__ void flush(const AttnParams &p) {
-        if (u0 < 0)
-            return;
-        wait_vmem();
-        if constexpr (kBlock)
-            __syncthreads();   // every wavefront's stores are complete
-        if (threadIdx.x == 0) {
-            atomicAdd(unit_counter(p, u0), 1);
-            if (u1 >= 0)
-                atomicAdd(unit_counter(p, u1), 1);
-        }
-    }
+    // kCombineInLaunch: called by every thread of the workgroup, at the end of
+    // its work; the first wavefront counts.
+    template <int D, bool kBlock>
+    __device__ __forceinline__ void flush(const AttnParams &p, const int *s_pre, int64_t ptot);
 };
 
 // Sums of waves 1 .. kWaves - 1 of a workgroup added into wave 0's `a` (the
@@ -405,22 +400,45 @@ __device__ void combine_waves(Acc<VE> &a, float *comb, int wave, int lane) {
 // only while the merge workgroups fill at most half of the slots of every XCD.
 // Of two overlapping calls at least one then finds room for its workers beside
 // the other's merge workgroups on every XCD, finishes, and frees the other.
-// (Three calls and more can fill an XCD between them.)  The wait is bounded
-// all the same (kMergeSpins polls); a wavefront that gives up writes NaN, so
-// such a failure shows in the output instead of as a hang.
+// Three calls and more can fill an XCD between them.  So the wait is bounded
+// (p.merge_polls polls): a merge wavefront that has waited that long leaves,
+// which frees its slot, and the worker that arrives last on the unit merges
+// the unit's rows in its place.  Nothing in a launch thus depends on the order
+// or the place in which its workgroups start.
 //
-// Counter protocol: the unit's counter reaches nparts once every worker has
-// arrived; then each merge wavefront of the unit with a valid row adds one
-// after it has read the partials, and the last of them sets the counter back
-// to zero for the next call.  The host spaces the counters of the units
-// apart (cnt_shift): with all of them on one line, every worker's arrival
-// and every merge wavefront's poll queued on that line, which made the
-// block-draft call 38 % slower.
-constexpr int kMergeSpins = 1 << 22;
+// Counter protocol: the unit's word counts arrivals of workers (low 32 bits),
+// merge wavefronts that are through with the unit (16 bits) and those of them
+// that left without the partials (16 bits), all in single 64-bit atomic
+// additions.  Each of the nparts workers and of the merge wavefronts with a
+// valid row adds exactly once:
+//   * a merge wavefront that saw all arrivals reads the partials, then adds
+//     kMergeDone;
+//   * one that gives up adds kMergeDone + kMergeLeft.  If that finds all
+//     arrivals counted, it merges its row after all; if not, the worker whose
+//     arrival is the last finds kMergeLeft counted and merges every row of the
+//     unit (rows that other wavefronts merge too get the same values twice);
+//   * whoever adds last, by the counts, sets the word back to zero for the
+//     next call.
+// The host spaces the words of the units apart (cnt_shift, at least 9 in this
+// mode): with all of them on one line, every worker's arrival and every merge
+// wavefront's poll queued on that line, which made the block-draft call 38 %
+// slower.
+typedef unsigned long long unit_word_t;
+constexpr unit_word_t kMergeDone = 1ull << 32, kMergeLeft = 1ull << 48;
+__device__ __forceinline__ uint32_t word_arrived(unit_word_t w) { return (uint32_t)w; }
+__device__ __forceinline__ int word_done(unit_word_t w) { return (int)((w >> 32) & 0xffff); }
+__device__ __forceinline__ int word_left(unit_word_t w) { return (int)(w >> 48); }
+__device__ __forceinline__ unit_word_t *unit_word(const AttnParams &p, int unit) {
+    return reinterpret_cast<unit_word_t *>(unit_counter(p, unit));
+}
+__device__ __forceinline__ void clear_word(unit_word_t *w) {
+    __hip_atomic_store(w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
-// Waits until *c >= target; false if kMergeSpins polls saw less.
-__device__ __forceinline__ bool wait_count(const int *c, int target) {
-    for (int i = 0; i < kMergeSpins; i++) {
+// Waits until `target` workers have arrived; false if `polls` polls saw less.
+__device__ __forceinline__ bool wait_arrivals(const unit_word_t *w, int target, int polls) {
+    const int *c = reinterpret_cast<const int *>(w);   // the low half
+    for (int i = 0; i < polls; i++) {
         const int v = first_lane_int(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         if (v >= target) {
             __atomic_signal_fence(__ATOMIC_SEQ_CST);   // later loads stay after the poll
@@ -445,6 +463,11 @@ __device__ __forceinline__ void combine_lane_groups(Acc<VE> &a) {
     a.M = Mall;
 }
 
+// Draft rows of unit (b, .) with i < q_len: the merge wavefronts that count.
+__device__ __forceinline__ int valid_rows(const AttnParams &p, int b) {
+    return min(p.rows_per_unit, ld_meta(p.q_lens, b) * p.G);
+}
+
 // Combines and writes row r of unit `unit` (one wavefront).
 template <int D>
 __device__ void merge_in_launch(const AttnParams &p, const int *s_pre, int unit, int r) {
@@ -452,7 +475,7 @@ __device__ void merge_in_launch(const AttnParams &p, const int *s_pre, int unit,
     const int np = s_pre[b + 1] - s_pre[b];
     if (np == 0)
         return;
-    const int nvalid = min(p.rows_per_unit, ld_meta(p.q_lens, b) * p.G);   // rows with i < q_len
+    const int nvalid = valid_rows(p, b);
     if (r >= nvalid)
         return;
     const int64_t ptot = (int64_t)p.Hkv * s_pre[p.B];
@@ -461,7 +484,7 @@ __device__ void merge_in_launch(const AttnParams &p, const int *s_pre, int unit,
     if (u.wlo == u.whi)
         return;   // one worker saw the whole unit and wrote `out`
     const int lane = threadIdx.x & 63;
-    int *cnt = unit_counter(p, unit);
+    unit_word_t *word = unit_word(p, unit);
     // Up to 4 * kMergeBatch pieces: where they lie is worked out before the
     // wait, so that only the loads follow it.
     constexpr int VE = D / 16;
@@ -472,31 +495,116 @@ __device__ void merge_in_launch(const AttnParams &p, const int *s_pre, int unit,
         at[k] = (uint32_t)u.slot(kk < u.nparts ? kk : 0) * (uint32_t)p.rows_per_unit + (uint32_t)r;
     }
     const int nmine = (u.nparts - (lane >> 4) + 3) >> 2;   // this lane group's pieces
-    const bool ok = wait_count(cnt, u.nparts);
+    const bool seen = wait_arrivals(word, u.nparts, p.merge_polls);
+    unit_word_t old = 0;
+    if (__builtin_expect(!seen, 0)) {
+        if (lane == 0)
+            old = atomicAdd(word, kMergeDone + kMergeLeft);
+        if (first_lane_int((int)word_arrived(old)) != u.nparts)
+            return;   // the last worker to arrive merges the row
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    }
     Acc<VE> a;
     a.init();
-    if (ok && u.nparts <= 4 * kMergeBatch) {
+    if (u.nparts <= 4 * kMergeBatch) {
         // 16 pieces and fewer take half of the loads (wavefront-uniform)
         if (u.nparts <= 2 * kMergeBatch)
             a.template add_at<D, kMergeBatch / 2>(p, at, nmine, lane & 15);
         else
             a.template add_at<D, kMergeBatch>(p, at, nmine, lane & 15);
-    } else if (ok) {
-        gather_partials<D, true>(p, u, r, lane & 15, lane >> 4, 4, a);
     } else {
-#pragma unroll
-        for (int e = 0; e < D / 16; e++)
-            a.acc[e] = __builtin_nanf("");
-        a.den = 1.0f;
-        a.M = 0.0f;
+        gather_partials<D, true>(p, u, r, lane & 15, lane >> 4, 4, a);
     }
     combine_lane_groups(a);
     if (lane < 16)
         write_merged<D>(p, b, g, r, lane, a);
     if (lane == 0) {
-        const int old = atomicAdd(cnt, 1);
-        if (old == u.nparts + nvalid - 1)   // nvalid merge wavefronts per unit
-            __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (seen)
+            old = atomicAdd(word, kMergeDone);
+        if (word_done(old) == nvalid - 1)   // all workers have arrived
+            clear_word(word);
+    }
+}
+
+// The rows of a unit whose merge wavefronts left, by the wavefront that
+// counted the last arrival: the sums of merge_in_launch in its order (so the
+// same values), but small rather than fast code, since it runs only when a
+// call was held up.
+template <int D>
+__device__ void merge_rows(const AttnParams &p, const UnitSplit &u, int b, int g, int nvalid, int lane) {
+    constexpr int VE = D / 16;
+    const int part = lane & 15;
+#pragma unroll 1
+    for (int r = 0; r < nvalid; r++) {
+        Acc<VE> a;
+        a.init();
+#pragma unroll 1
+        for (int kb = lane >> 4; kb < u.nparts; kb += 4 * kMergeBatch) {
+            const int ke = min(kb + 4 * kMergeBatch, u.nparts);
+            float Mb = a.M;
+#pragma unroll 1
+            for (int k = kb; k < ke; k += 4)
+                Mb = fmaxf(Mb, ld_coherent(p.ws_lse + (size_t)u.slot(k) * p.rows_per_unit + r));
+            if (Mb == -INFINITY)
+                continue;
+            a.rescale(Mb);
+#pragma unroll 1
+            for (int k = kb; k < ke; k += 4) {
+                const size_t row = (size_t)u.slot(k) * p.rows_per_unit + r;
+                float l[1] = {ld_coherent(p.ws_lse + row)};
+                float4 v[1][VE / 4];
+#pragma unroll
+                for (int e = 0; e < VE / 4; e++) {
+                    const f32x4_t t = ld_partial16(p, row * D + VE * part + 4 * e);
+                    v[0][e] = make_float4(t[0], t[1], t[2], t[3]);
+                }
+                a.template add_weighted<1>(l, v);
+            }
+        }
+        combine_lane_groups(a);
+        if (lane < 16)
+            write_merged<D>(p, b, g, r, lane, a);
+    }
+}
+
+// The first wavefront counts the workgroup's arrivals, lane 0 on the unit its
+// range starts in, lane 1 on the one it ends in.  What it has to do for merge
+// wavefronts that left is decided by the counts found.
+template <int D, bool kBlock>
+__device__ __forceinline__ void Arrivals::flush(const AttnParams &p, const int *s_pre, int64_t ptot) {
+    if (u0 < 0)
+        return;
+    wait_vmem();
+    if constexpr (kBlock) {
+        __syncthreads();   // every wavefront's stores are complete
+        if (threadIdx.x >= kWave)
+            return;
+    }
+    const int lane = threadIdx.x;
+    unit_word_t old = 0;
+    if (lane < 2 && (lane ? u1 : u0) >= 0)
+        old = atomicAdd(unit_word(p, lane ? u1 : u0), 1ull);
+    // no merge wavefront is through with the unit: none has left, and others
+    // will add after this one
+    if (__builtin_expect(!__any(word_done(old) != 0), 1))
+        return;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll 1
+    for (int k = 0; k < 2; k++) {
+        const int unit = k ? u1 : u0;
+        const int arrived = __builtin_amdgcn_readlane((int)word_arrived(old), k);
+        const int through = __builtin_amdgcn_readlane((int)(old >> 32), k);
+        if (unit < 0 || through == 0)
+            continue;
+        const int b = unit / p.Hkv, g = unit % p.Hkv;
+        const UnitSplit u = split_of(p, s_pre, unit, ptot);
+        if (arrived != u.nparts - 1)
+            continue;
+        const int nvalid = valid_rows(p, b);
+        if (word_left((unit_word_t)(uint32_t)through << 32))
+            merge_rows<D>(p, u, b, g, nvalid, lane);
+        if (lane == 0 && (through & 0xffff) == nvalid)
+            clear_word(unit_word(p, unit));
     }
 }
 

@@ -597,7 +597,7 @@ __global__ __launch_bounds__(64) void verify_kernel(AttnParams p) {
             x = s.next;
         }
     }
-    arr.flush<false>(p);
+    arr.template flush<D, false>(p, s_pre, ptot);
 }
 
 // Groups: a workgroup of kGroupWaves wavefronts is one worker.  Its range of
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(kGroupWaves * kWave, NB == 1 ? 2 : 1) void verify_g
     if (p.combine == kCombineLast)
         arr.template combine_last<D>(p, s_pre, ptot, gl.last);
     else
-        arr.flush<true>(p);
+        arr.template flush<D, true>(p, s_pre, ptot);
 }
 
 }  // namespace

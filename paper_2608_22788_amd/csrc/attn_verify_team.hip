@@ -460,7 +460,7 @@ __global__ __launch_bounds__(256) void verify_team_kernel(AttnParams p) {
         arr.add(p, s);
         x = s.next;
     }
-    arr.flush<true>(p);
+    arr.template flush<kD, true>(p, s_pre, ptot);
 }
 
 }  // namespace

@@ -16,6 +16,7 @@
 
 #include <mutex>
 
+#include "attn_common.h"
 #include "ts_attn.h"
 #include "ts_internal.h"
 
@@ -81,7 +82,7 @@ extern "C" int ts_decode_attn_noalloc(const ts_attn_shape *shape, const void *q,
         if (st)
             return st;
         return launch_attn(shape, q, k_pages, v_pages, page_table, ctx_lens, q_lens, out, scale, ws,
-                           kScratchBytes, stream, nullptr, nullptr);
+                           kScratchBytes, stream, nullptr, nullptr, kMergePolls);
     } catch (...) {
         return fail(TS_ERR_HIP, "unexpected C++ exception");
     }

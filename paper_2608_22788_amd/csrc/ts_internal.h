@@ -23,9 +23,10 @@ int check_device();
 int check_shape(const ts_attn_shape *s);
 // The body of ts_decode_attn / ts_decode_attn_events: validates, plans and
 // enqueues the call on `stream` with the given workspace (allocates nothing).
+// merge_polls: kMergePolls, or what a test sets instead.
 int launch_attn(const ts_attn_shape *s, const void *q, const void *k_pages, const void *v_pages,
                 const int32_t *page_table, const int32_t *ctx_lens, const int32_t *q_lens, void *out,
                 float scale, void *workspace, size_t workspace_bytes, void *stream, void *ev_begin,
-                void *ev_end);
+                void *ev_end, int merge_polls);
 
 }  // namespace tsattn
