@@ -125,7 +125,9 @@ typedef struct ts_attn_shape {
 
 /* Bytes of device workspace ts_decode_attn needs for this shape (split-KV
  * partial outputs, their log-sum-exp, the per-unit arrival counters and the
- * TS_DEBUG flag word).
+ * TS_DEBUG flag word).  TS_VARIANT_AUTO and TS_VARIANT_WAVE with num_workers 0
+ * need the same wherever AUTO runs the single-wavefront streams (up to 32 rows
+ * per unit at head_dim 128, always at head_dim 64).
  * Host only; returns 0 and sets ts_last_error() for an unsupported shape. */
 size_t ts_decode_attn_workspace_size(const ts_attn_shape *shape);
 

@@ -134,8 +134,8 @@ static int auto_workers(const ts_attn_shape *s, bool q1, bool team, int rows) {
 // pages per worker lengthen the chain of the smallest calls (one sequence of
 // 1,600 tokens: 11.8 against 10.7 us).  Nor more than single wavefronts would
 // be, which bounds the pieces of a call with very few units (4 units of 1,300
-// tokens: 11.5 us with 15 pieces each, 12.0 with 30) and keeps every workspace
-// that was large enough for them large enough.
+// tokens: 11.5 us with 15 pieces each, 12.0 with 30) and by the workspace, which
+// is sized for those.
 static int group_workers(const ts_attn_shape *s, int rows) {
     const int64_t pages_ub = (int64_t)s->num_seqs * s->num_kv_heads *
                              ((s->max_ctx_len + kPage - 1) / kPage);
@@ -248,8 +248,11 @@ int make_plan(const ts_attn_shape *s, Plan *pl) {
     // Workspace: the split counters first, at a fixed size whatever the shape,
     // so that no call's partial results ever land on them (they are zero
     // between calls); then 256 bytes for the TS_DEBUG check's flag word; then
-    // the partial outputs and their log-sum-exp.
-    const size_t slots = 2 * (size_t)pl->W;
+    // the partial outputs and their log-sum-exp, with slots for as many workers
+    // as single wavefronts would be where groups run: a caller's workspace for
+    // TS_VARIANT_AUTO then also serves TS_VARIANT_WAVE with the same shape.
+    const int ws_workers = pl->group ? auto_workers(s, false, false, pl->rows_per_unit) : pl->W;
+    const size_t slots = 2 * (size_t)ws_workers;
     pl->ws_cnt_off = 0;
     pl->ws_dbg_off = kCounterBytes;
     pl->ws_o_off = pl->ws_dbg_off + 256;

@@ -33,7 +33,7 @@ def test_range_begin_at_the_top_of_its_range():
 
 def test_groups_need_no_larger_workspace_than_single_wavefronts():
     """The automatic kernel choice fits every workspace that was sized for
-    single-wavefront workers (TS_VARIANT_WAVE)."""
+    single-wavefront workers (TS_VARIANT_WAVE), and the other way round."""
     from paper_2608_22788_amd import binding
     for B in (1, 2, 3, 8, 40, 300):
         for hkv in (1, 2, 8):
@@ -43,3 +43,4 @@ def test_groups_need_no_larger_workspace_than_single_wavefronts():
                     size = [binding.workspace_size(binding.make_shape(B, G * hkv, hkv, D, Q, maxp, ctx, B * maxp, 0, 16, v))
                             for v in (0, 1)]
                     assert 0 < size[0] <= size[1], (B, hkv, ctx, G, Q, D, size)
+                    assert size[0] == size[1], (B, hkv, ctx, G, Q, D, size)
