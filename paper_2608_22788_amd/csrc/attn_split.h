@@ -41,6 +41,15 @@ __device__ __forceinline__ void st_coherent(float *p, float v) {
 __device__ __forceinline__ block_rsrc_t partial_rsrc(const AttnParams &p) {
     return block_rsrc(p.ws_o, p.ws_o_bytes);
 }
+// The log-sum-exp area behind it: one float per row of D.
+template <int D>
+__device__ __forceinline__ block_rsrc_t lse_rsrc(const AttnParams &p) {
+    return block_rsrc(p.ws_lse, p.ws_o_bytes / D);
+}
+// A row past both areas (which hold less than 2^31 and 2^31 / D bytes): loads
+// from it return zeros and touch no memory.
+template <int D>
+constexpr uint32_t kNoRow = (1u << 31) / (D * sizeof(float));
 // Partial-area elements elem .. elem + 3 (elem a multiple of 4).
 __device__ __forceinline__ void st_partial16(const AttnParams &p, size_t elem, f32x4_t v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), partial_rsrc(p),
@@ -113,7 +122,9 @@ struct Acc {
         den = 0.0f;
         M = -INFINITY;
     }
-    // Adds a batch of up to kB partials (n valid) given their rows.
+    // Adds a batch of up to kB partials (n valid) given their rows.  What is
+    // not valid is not read and counts as zeros: another partial's values in
+    // its place may be infinite, and a weight of 0 would make them NaN.
     // kCoherent: read them with device-coherent loads (partials written by
     // other workers of the same launch), else with plain vector loads.
     template <int D, bool kCoherent, int kB>
@@ -122,17 +133,22 @@ struct Acc {
         float4 v[kB][VE / 4];
 #pragma unroll
         for (int k = 0; k < kB; k++) {
-            const size_t row = rows[k < n ? k : 0];
-            const float *src = p.ws_o + row * D + VE * part;
+            l[k] = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < VE / 4; e++)
+                v[k][e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (k >= n)
+                continue;
+            const float *src = p.ws_o + rows[k] * D + VE * part;
             if constexpr (kCoherent) {
-                l[k] = k < n ? ld_coherent(p.ws_lse + row) : -INFINITY;
+                l[k] = ld_coherent(p.ws_lse + rows[k]);
 #pragma unroll
                 for (int e = 0; e < VE / 4; e++) {
-                    const f32x4_t t = ld_partial16(p, row * D + VE * part + 4 * e);
+                    const f32x4_t t = ld_partial16(p, rows[k] * D + VE * part + 4 * e);
                     v[k][e] = make_float4(t[0], t[1], t[2], t[3]);
                 }
             } else {
-                l[k] = k < n ? p.ws_lse[row] : -INFINITY;
+                l[k] = p.ws_lse[rows[k]];
 #pragma unroll
                 for (int e = 0; e < VE / 4; e++)
                     v[k][e] = *reinterpret_cast<const float4 *>(src + 4 * e);
@@ -140,15 +156,16 @@ struct Acc {
         }
         add_loaded<kB>(l, v);
     }
-    // Adds the first n (of up to kB) partials at rows at[0 .. n - 1] of the
-    // partial area, with device-coherent loads.
+    // Adds the partials at rows at[0 .. kB - 1] of the partial area, with
+    // device-coherent loads; the first n are rows, the others kNoRow<D>.
     template <int D, int kB>
     __device__ void add_at(const AttnParams &p, const uint32_t *at, int n, int part) {
         float l[kB];
         float4 v[kB][VE / 4];
 #pragma unroll
         for (int k = 0; k < kB; k++) {
-            l[k] = ld_coherent(p.ws_lse + at[k]);
+            l[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                lse_rsrc<D>(p), (int)(at[k] * (uint32_t)sizeof(float)), 0, kDeviceScope));
 #pragma unroll
             for (int e = 0; e < VE / 4; e++) {
                 const f32x4_t t = ld_partial16(p, (size_t)(at[k] * (uint32_t)D + (uint32_t)(VE * part + 4 * e)));
@@ -160,7 +177,8 @@ struct Acc {
             l[k] = k < n ? l[k] : -INFINITY;
         add_loaded<kB>(l, v);
     }
-    // Adds kB partials held in registers (those with l = -inf count nothing).
+    // Adds kB partials held in registers (those with l = -inf count nothing;
+    // their values are zero or finite, so a weight of 0 does).
     template <int kB>
     __device__ void add_loaded(const float (&l)[kB], const float4 (&v)[kB][VE / 4]) {
         float Mb = M;
@@ -492,7 +510,7 @@ __device__ void merge_in_launch(const AttnParams &p, const int *s_pre, int unit,
 #pragma unroll
     for (int k = 0; k < kMergeBatch; k++) {
         const int kk = (lane >> 4) + 4 * k;
-        at[k] = (uint32_t)u.slot(kk < u.nparts ? kk : 0) * (uint32_t)p.rows_per_unit + (uint32_t)r;
+        at[k] = kk < u.nparts ? (uint32_t)u.slot(kk) * (uint32_t)p.rows_per_unit + (uint32_t)r : kNoRow<D>;
     }
     const int nmine = (u.nparts - (lane >> 4) + 3) >> 2;   // this lane group's pieces
     const bool seen = wait_arrivals(word, u.nparts, p.merge_polls);

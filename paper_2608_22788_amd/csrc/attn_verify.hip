@@ -523,6 +523,8 @@ struct Verify {
                 a.init();
 #pragma unroll
                 for (int k = 0; k < kGroupWaves; k++) {
+                    if (!on[k])
+                        continue;   // not a weight of 0: record k0's sums may be infinite
                     const float f = m[k] == -INFINITY ? 0.0f : fast_exp2(m[k] - M);
                     a.den += f * l[k];
 #pragma unroll

@@ -56,3 +56,33 @@ def test_group_kernel(orc, case):
         canary_ok(t, wl)
         torch.cuda.synchronize()
         assert int(ws[:1 << 20].count_nonzero()) == 0, f"counters left set: {name}"
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("name", ["short_long", "two_blocks", "merge_kernel", "last", "last_two_blocks", "d64_4"])
+def test_infinite_value_stays_in_its_column(name, variant):
+    """An infinite value of a sequence's first token makes its dim of every
+    output row infinite and leaves the others as they are bit for bit, wherever
+    the unit is split and however its pieces meet (a piece that is read in place
+    of a missing one, with weight 0, would turn it into NaN)."""
+    import torch
+    from paper_2608_22788_amd import binding, device
+    _, Hq, Hkv, D, Qmax, ql, cl, _ = next(c for c in CASES if c[0] == name)
+    if variant == 2 and D == 64:
+        pytest.skip("the team kernel is for head_dim 128")
+    cfg = dict(B=len(ql), Hq=Hq, Hkv=Hkv, D=D, q_len=1, lengths=("uniform", 1, 1), scale=D ** -0.5)
+    wl = synth.make_workload(f"inf_{name}", seed=78, cfg=cfg, ctx_lens=cl, q_lens=ql, Qmax=Qmax)
+    t = device.upload(wl)
+    say(f"infinite value {name} variant={variant}")
+    device.run(wl, t, variant=variant)
+    want = t["out"].clone()
+    first = t["page_table"][:, 0].long()
+    on = torch.tensor([b for b in range(wl.B) if ql[b] > 0], device="cuda")
+    t["v_pages"][first[on], :, 0, 5] = float("inf")
+    for b in range(wl.B):
+        want[b, :ql[b], :, 5] = float("inf")
+    device.run(wl, t, variant=variant)
+    torch.cuda.synchronize()
+    got, exp = t["out"].view(torch.int16), want.view(torch.int16)
+    bad = [b for b in range(wl.B) if not torch.equal(got[b, :ql[b]], exp[b, :ql[b]])]
+    assert not bad, f"sequences {bad[:10]} of {len(bad)}"
