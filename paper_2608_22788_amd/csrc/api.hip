@@ -143,6 +143,10 @@ static int group_workers(const ts_attn_shape *s, int rows) {
                                    auto_workers(s, false, false, rows)});
 }
 
+// Ranges that the kernel of a plan cuts the call's pages into: one per worker,
+// or one per wavefront of a group.
+static int plan_ranges(const Plan &pl) { return pl.group ? kGroupWaves * pl.W : pl.W; }
+
 // Workgroups of `k` resident per compute unit times the compute units, or 0
 // if the runtime cannot tell.  The LDS size is rounded up to 4 KiB (the
 // answer is then a lower bound, never an overestimate), so the cache keeps
@@ -449,7 +453,7 @@ int launch_attn(const ts_attn_shape *s, const void *q, const void *k_pages, cons
     p.G = pl.G;
     p.rows_per_unit = pl.rows_per_unit;
     p.W = pl.W;
-    p.range_inv = 0xffffffffu / (uint32_t)(pl.group ? kGroupWaves * pl.W : pl.W);
+    p.range_inv = range_reciprocal(plan_ranges(pl));
     p.ws_o_bytes = L.ws_o_bytes;
     p.combine = (int8_t)L.combine;
     p.cnt_shift = (int8_t)L.cnt_shift;

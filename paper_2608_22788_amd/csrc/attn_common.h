@@ -1,11 +1,12 @@
 // attn_common.h -- device-side pieces shared by the paged-attention kernels:
 // kernel parameters, bf16 packing, wavefront reductions and the split of the
-// KV stream over wavefronts.
+// KV stream over workers.
 //
 // Work partition.  A "unit" is one (sequence b, KV head g) pair; it owns
 // np_b = ceil(L_b / 16) pages.  Units are laid end to end (b-major, g-minor)
 // into one global page index space of Ptot = Hkv * sum_b np_b pages, and
-// worker (wavefront) w of W processes the contiguous range
+// worker w of W (a wavefront, a group or a team of four) processes the
+// contiguous range
 //   [floor(Ptot * w / W), floor(Ptot * (w + 1) / W)),
 // so every worker streams the same number of KV bytes to within one page no
 // matter how skewed the context lengths are.  A worker's range may start or
@@ -23,6 +24,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include "partition.h"
 
 namespace tsattn {
 
@@ -58,10 +61,10 @@ struct AttnParams {   // 128 bytes of kernel arguments
     float *ws_lse;              // [2W][rows_per_unit] fp32 log2-sum-exp
     int *counters;              // arrivals per split unit, unit u at u << cnt_shift (zero between calls)
     int B, Hq, Hkv, Qmax, max_pages;
-    uint32_t range_inv;         // floor((2^32 - 1) / ranges), ranges = W, or kGroupWaves W for groups
+    uint32_t range_inv;         // range_reciprocal(ranges), ranges = W, or kGroupWaves W for groups
     int G;                      // Hq / Hkv
     int rows_per_unit;          // G * Qmax
-    int W;                      // workers (wavefronts)
+    int W;                      // workers (wavefronts, groups or teams)
     int ws_o_bytes;             // bytes of the partial area (set unless kCombineKernel; < 2^31)
     int8_t combine;             // kCombine*: who combines the split partials
     int8_t cnt_shift;           // log2 of the ints between the counters of consecutive units
@@ -280,25 +283,9 @@ __device__ __forceinline__ int xcd_worker(int block, int W) {
     return x * (W / kXcds) + min(x, W % kXcds) + s;
 }
 
-__device__ __forceinline__ int64_t worker_begin(int64_t ptot, int w, int W) {
-    return (ptot * (int64_t)w) / (int64_t)W;
-}
-
-// The same for range w of `ranges`, p.range_inv being floor((2^32 - 1) /
-// ranges): in 32 bits the high word of the product with it is at most one
-// below the quotient, since it differs from the exact value by less than
-// x / 2^32 < 1.
+// Start of range w of `ranges` (p.range_inv is their reciprocal).
 __device__ __forceinline__ int64_t range_begin(const AttnParams &p, int64_t ptot, int w, int ranges) {
-    const uint64_t x = (uint64_t)ptot * (uint32_t)w;
-    if (x >> 32)
-        return worker_begin(ptot, w, ranges);
-    const uint32_t q = __umulhi((uint32_t)x, p.range_inv);
-    return q + ((uint32_t)x - q * (uint32_t)ranges >= (uint32_t)ranges);
-}
-
-// Worker whose range holds global page x (0 <= x < ptot).
-__device__ __forceinline__ int worker_of(int64_t ptot, int64_t x, int W) {
-    return (int)(((x + 1) * (int64_t)W - 1) / ptot);
+    return range_start(ptot, w, ranges, p.range_inv);
 }
 
 // Sequence holding global page x: the largest b with Hkv * s_pre[b] <= x.

@@ -75,41 +75,6 @@ __device__ __forceinline__ void wait_vmem() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-// The workers whose ranges meet the unit that occupies global pages
-// [us, us + np), and the workspace slot of the k-th piece (k = 0 .. nparts-1,
-// in worker order).  When every worker has at least one page (ptot >= W),
-// worker wlo + k, k > 0, began inside the unit (slot 2 (wlo + k)) and only
-// wlo's start needs comparing with us.  Otherwise every range holds at most
-// one page, so page us + k of the unit is the whole range of worker
-// worker_of(us + k), which began there (slot 2 worker_of(us + k)).
-struct UnitSplit {
-    int64_t ptot;     // pages of the whole call
-    int64_t us;       // global index of the unit's first page
-    int W;            // workers
-    int wlo, whi;     // first and last worker whose range meets the unit
-    int first_slot;   // slot of worker wlo's piece
-    bool dense;       // ptot >= W
-    int nparts;       // workers with a non-empty piece of the unit
-    __device__ __forceinline__ int slot(int k) const {
-        if (dense)
-            return k == 0 ? first_slot : 2 * (wlo + k);
-        return 2 * worker_of(ptot, us + k, W);
-    }
-};
-
-__device__ __forceinline__ UnitSplit unit_split(int64_t ptot, int64_t us, int np, int W) {
-    UnitSplit u;
-    u.ptot = ptot;
-    u.us = us;
-    u.W = W;
-    u.wlo = worker_of(ptot, us, W);
-    u.whi = worker_of(ptot, us + np - 1, W);
-    u.dense = ptot >= W;
-    u.first_slot = worker_begin(ptot, u.wlo, W) >= us ? 2 * u.wlo : 2 * u.wlo + 1;
-    u.nparts = u.dense ? u.whi - u.wlo + 1 : np;
-    return u;
-}
-
 // Running log-sum-exp combination of partials for one lane's VE dims.
 template <int VE>
 struct Acc {

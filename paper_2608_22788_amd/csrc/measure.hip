@@ -206,7 +206,7 @@ int ts_page_gather_read(const ts_attn_shape *s, const void *k_pages, const void 
     p.Qmax = s->max_q_len;
     p.max_pages = s->max_pages_per_seq;
     p.W = W;
-    p.range_inv = 0xffffffffu / (uint32_t)W;
+    p.range_inv = range_reciprocal(W);
     void (*k)(AttnParams, uint32_t *) = s->head_dim == 64 ? page_gather_kernel<64> : page_gather_kernel<128>;
     uint32_t *out = static_cast<uint32_t *>(sink);
     void *args[] = {&p, &out};
