@@ -244,11 +244,12 @@ def test_in_kernel_combine_with_many_pieces(dev, orc, Qmax):
             assert_parity(got, ref, f"manypieces v{var} w{w}")
 
 
-# Few units with many pieces each (workers >= 8 x units) and at most 512
+# Few units with many pieces each (workers >= 8 x units, or groups) and few
 # merge workgroups: merge wavefronts that follow the workers in the grid
 # combine the splits.  (name, Hq, Hkv, D, q_lens, ctx_lens); with the
-# automatic worker count: 16 units for 768 workers (256 merge wavefronts),
-# 32 units for 1,024 (128), 16 units for 512 teams (256 workgroups).
+# automatic kernel and worker count: 16 units for 256 groups (64 merge
+# workgroups), 32 units for 256 groups (32), 16 units for 512 teams (256);
+# single wavefronts: 16 units for 768 (256), 32 units for 1,024 (128).
 IN_LAUNCH = [
     ("verify_q4", 32, 8, 128, [4, 3], [20000, 3001]),              # one draft shorter than max_q_len
     ("decode_q1", 32, 8, 128, [1, 1, 1, 0], [9000, 40, 17000, 500]),  # a unit whole in one worker, a skipped sequence

@@ -110,25 +110,29 @@ def test_debug_mode_reports_bad_device_inputs():
 def test_concurrent_streams_with_their_own_workspaces():
     """Calls on two streams at once, each with its own workspace (the ABI's
     rule for concurrency), give bit for bit what the same calls give one
-    after the other.  Both workloads split their units (the bulk shape combines
-    in the kernel, the verify shape in the merge kernel), so both workspaces
-    are in use while the other stream runs."""
+    after the other.  Both workloads split their units (in the bulk shape the
+    last worker of a unit combines them, in the verify shape the merge kernel),
+    so both workspaces are in use while the other stream runs."""
     import torch
     from paper_2608_22788_amd import binding, device
     cfg_a = dict(B=256, Hq=32, Hkv=8, D=128, q_len=1, lengths=("uniform", 1, 1), scale=128 ** -0.5)
-    cfg_b = dict(B=4, Hq=32, Hkv=8, D=128, q_len=4, lengths=("uniform", 1, 1), scale=128 ** -0.5)
+    cfg_b = dict(B=12, Hq=32, Hkv=8, D=128, q_len=4, lengths=("uniform", 1, 1), scale=128 ** -0.5)
     rng = np.random.default_rng(7)
-    # 256 sequences x 8 KV heads = 2,048 units >= 2 x 1,024 workers: combined in the kernel
+    # 256 sequences x 8 KV heads = 2,048 units >= 2 x 256 workers: combined by the last arriver
     wa = synth.make_workload("streams_a", seed=11, cfg=cfg_a, ctx_lens=rng.integers(50, 1200, size=256).tolist(),
                              q_lens=[1] * 256)
-    wb = synth.make_workload("streams_b", seed=12, cfg=cfg_b, ctx_lens=[20000, 9000, 300, 15000], q_lens=[4] * 4)
+    # 12 x 8 units of 16 rows: 384 merge workgroups, more than the launch takes
+    wb = synth.make_workload("streams_b", seed=12, cfg=cfg_b, ctx_lens=[20000, 9000, 300, 15000] * 3,
+                             q_lens=[4] * 12)
     ta, tb = device.upload(wa, values="device"), device.upload(wb, values="device")
 
-    def ws_for(wl, t):
+    def ws_for(wl, t, combine):
         shape = binding.shape_of(t["q"], t["k_pages"], t["page_table"], wl.max_ctx_len)
+        plan = binding.decode_attn_plan(shape)
+        assert plan["combine"] == combine, plan
         return binding.new_workspace(binding.workspace_size(shape))
 
-    wsa, wsb = ws_for(wa, ta), ws_for(wb, tb)
+    wsa, wsb = ws_for(wa, ta, binding.COMBINE_LAST_ARRIVER), ws_for(wb, tb, binding.COMBINE_MERGE_KERNEL)
     device.run(wa, ta, workspace=wsa)
     device.run(wb, tb, workspace=wsb)
     torch.cuda.synchronize()
