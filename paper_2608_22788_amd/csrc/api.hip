@@ -388,9 +388,13 @@ static int finish_plan(const ts_attn_shape *s, Plan &pl, Launch &L) {
         // A unit meets about W / units + 1 workers.  Up to about three pieces
         // a unit, one wavefront per 4 rows takes every piece itself (a fourth
         // of the blocks); beyond that four wavefronts share each row group's
-        // pieces.  Measured: 1,024 units with 16-32 rows, 768-1,024 workers,
-        // 1.5-6 % faster per call; at 4 pieces a unit (32 skewed sequences)
-        // the long sequences' units made it 2 % slower, hence the bound.
+        // pieces.  Measured with single wavefronts: 1,024 units with 16-32 rows,
+        // 768-1,024 workers, 1.5-6 % faster per call; at 4 pieces a unit (32
+        // skewed sequences) the long sequences' units made it 2 % slower, hence
+        // the bound.  With groups (256 workers, so from 128 units): 2 % faster
+        // at 192 and 320 units of 16 rows, 3-5 % at 128 and 256 units of 32
+        // rows, 2 % slower at 128 units of 16 skewed sequences and 5 % at 128
+        // units of head_dim 64; below the line 2 % slower to 3 % faster.
         const bool few = (int64_t)pl.W <= 2 * units;
         L.merge_k = merge_variant(D, few);
         L.merge_blocks = units * (few ? (ngroups + 3) / 4 : ngroups);
