@@ -39,11 +39,11 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.md")
 # measured on.
 TRAFFIC_SOURCES = {
     "bulk": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify.hip", "csrc/api.hip",
-            "build.py"],
+             "build.py"],
     "mtp": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify.hip", "csrc/api.hip",
-           "build.py"],
-    "dflash": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify_team.hip", "csrc/api.hip",
-              "build.py"],
+            "build.py"],
+    "dflash": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify_team.hip",
+               "csrc/api.hip", "build.py"],
 }
 KERNELS = {"bulk": "verify_group_kernel<128,1>", "mtp": "verify_group_kernel<128,1>",
            "dflash": "verify_team_kernel<4>"}
