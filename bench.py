@@ -37,13 +37,12 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.md")
 # Files whose content decides the streaming kernel of each workload and its
 # launch; a traffic figure counts only while their hash matches the one it was
 # measured on.
+_TRAFFIC_COMMON = ["csrc/attn_common.h", "csrc/partition.h", "csrc/wave_scan.h", "csrc/attn_split.h", "csrc/api.hip",
+                   "build.py"]
 TRAFFIC_SOURCES = {
-    "bulk": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify.hip", "csrc/api.hip",
-             "build.py"],
-    "mtp": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify.hip", "csrc/api.hip",
-            "build.py"],
-    "dflash": ["csrc/attn_common.h", "csrc/partition.h", "csrc/attn_split.h", "csrc/attn_verify_team.hip",
-               "csrc/api.hip", "build.py"],
+    "bulk": _TRAFFIC_COMMON + ["csrc/attn_verify.hip"],
+    "mtp": _TRAFFIC_COMMON + ["csrc/attn_verify.hip"],
+    "dflash": _TRAFFIC_COMMON + ["csrc/attn_verify_team.hip"],
 }
 KERNELS = {"bulk": "verify_group_kernel<128,1>", "mtp": "verify_group_kernel<128,1>",
            "dflash": "verify_team_kernel<4>"}

@@ -26,6 +26,7 @@
 #include <stdint.h>
 
 #include "partition.h"
+#include "wave_scan.h"
 
 namespace tsattn {
 
@@ -204,22 +205,6 @@ __device__ __forceinline__ int seq_pages(const AttnParams &p, int b) {
     return (Q > 0 && L > 0) ? (L + kPage - 1) / kPage : 0;
 }
 
-// Inclusive scan over a wavefront in vector-ALU lane moves (no LDS round
-// trips): four shifts inside each row of 16 lanes, then the last lane of a row
-// into the next row and the last lane of the lower half into the upper.
-template <int CTRL, int kRows>
-__device__ __forceinline__ int scan_step_i32(int x) {
-    return x + __builtin_amdgcn_update_dpp(0, x, CTRL, kRows, 0xf, false);
-}
-__device__ __forceinline__ int wave_incl_scan_i32(int x) {
-    x = scan_step_i32<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8
-    x = scan_step_i32<0x112, 0xf>(x);
-    x = scan_step_i32<0x114, 0xf>(x);
-    x = scan_step_i32<0x118, 0xf>(x);
-    x = scan_step_i32<0x142, 0xa>(x);   // row_bcast:15
-    return scan_step_i32<0x143, 0xc>(x);   // row_bcast:31
-}
-
 // Exclusive prefix of seq_pages into s_pre[0..B] (s_pre[B] = total), computed
 // by the first wavefront of the block; every thread must call it (it ends in
 // a block barrier).  Up to 64 sequences take one lane each.  More are taken in
@@ -235,7 +220,7 @@ __device__ inline void page_prefix(const AttnParams &p, int *s_pre) {
         const int lane = threadIdx.x;
         const int v = seq_pages(p, min(lane, p.B - 1));
         const int n = lane < p.B ? v : 0;
-        const int incl = wave_incl_scan_i32(n);
+        const int incl = wave_incl_scan(n);
         if (lane < p.B)
             s_pre[lane] = incl - n;
         if (lane == p.B - 1)
@@ -256,7 +241,7 @@ __device__ inline void page_prefix(const AttnParams &p, int *s_pre) {
                 n[k] = b < p.B ? v : 0;
                 run += n[k];
             }
-            const int incl = wave_incl_scan_i32(run);
+            const int incl = wave_incl_scan(run);
             int acc = base + incl - run;
 #pragma unroll
             for (int k = 0; k < kPrefixRun; k++) {

@@ -49,6 +49,7 @@
 
 #include "ts_attn.h"
 #include "ts_internal.h"
+#include "wave_scan.h"
 
 namespace tsattn {
 
@@ -212,35 +213,13 @@ __device__ __forceinline__ Fx fx_shfl(Fx a, int lane) {
     return Fx{__shfl(a.w0, lane, kWave), __shfl(a.w1, lane, kWave), __shfl(a.w2, lane, kWave)};
 }
 
-// One step of a wavefront scan: the value CTRL moves into this lane, zero
-// where it moves none (rows outside kRows, or no source lane).
 template <int CTRL, int kRows>
-__device__ __forceinline__ uint64_t dpp_u64(uint64_t x) {
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, kRows, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, kRows, 0xf, false);
-    return (uint64_t)hi << 32 | lo;
+__device__ __forceinline__ Fx lane_move(Fx x) {
+    return Fx{tsattn::lane_move<CTRL, kRows>(x.w0), tsattn::lane_move<CTRL, kRows>(x.w1),
+              tsattn::lane_move<CTRL, kRows>(x.w2)};
 }
-template <int CTRL, int kRows>
-__device__ __forceinline__ Fx scan_step(Fx x) {
-    return fx_add(x, Fx{dpp_u64<CTRL, kRows>(x.w0), dpp_u64<CTRL, kRows>(x.w1), dpp_u64<CTRL, kRows>(x.w2)});
-}
-template <int CTRL, int kRows>
-__device__ __forceinline__ double scan_step(double x) {
-    return x + __longlong_as_double((long long)dpp_u64<CTRL, kRows>((uint64_t)__double_as_longlong(x)));
-}
-
-// Inclusive scan over a wavefront in vector-ALU lane moves (no LDS
-// round trips): four shifts inside each row of 16 lanes, then the last lane of
-// a row into the next row and the last lane of the lower half into the upper.
-constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-template <typename T>
-__device__ __forceinline__ T wave_incl_scan(T x) {
-    x = scan_step<kRowShr + 1, 0xf>(x);
-    x = scan_step<kRowShr + 2, 0xf>(x);
-    x = scan_step<kRowShr + 4, 0xf>(x);
-    x = scan_step<kRowShr + 8, 0xf>(x);
-    x = scan_step<kRowBcast15, 0xa>(x);
-    return scan_step<kRowBcast31, 0xc>(x);
+__device__ __forceinline__ Fx fx_incl_scan(Fx x) {
+    return wave_incl_scan(x, [](Fx a, Fx b) { return fx_add(a, b); });
 }
 
 // ---- exact sums in float64 ------------------------------------------------------
@@ -540,7 +519,7 @@ __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams 
             for (int c = 0; c < kPickChunk; c++)
                 run = fx_add(run, v[c]);
         }
-        incl = wave_incl_scan(run);
+        incl = fx_incl_scan(run);
         Z = fx_shfl(incl, kWave - 1);
         // leftover mass zero: sample p_k itself (its sums are in pass 1)
         if (pass == 0 && rejected && fx_is_zero(Z))
@@ -593,7 +572,7 @@ __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams 
         load_rows<false, false>(a, b, k, blk, 4 * kQuads * lane, 4, r);
         lane_sum = fx_of_bins(sum_rows<false>(r));
     }
-    const Fx lincl = fx_add(base, wave_incl_scan(lane_sum));
+    const Fx lincl = fx_add(base, fx_incl_scan(lane_sum));
     const unsigned long long hit = __ballot(fx_gt(lincl, T));
     const int first = __ffsll((long long)hit) - 1;   // exists: the block's total exceeds T
     const Fx before = fx_shfl(fx_sub(lincl, lane_sum), first);
@@ -608,7 +587,7 @@ __global__ __launch_bounds__(kPickThreads) void accept_pick_kernel(AcceptParams 
         qm = lane == m ? qf : qm;
     }
     const Fx w = pm > qm ? fx_sub(fx_of_prob(pm), fx_of_prob(qm)) : fx_zero();
-    const Fx eincl = fx_add(before, wave_incl_scan(w));
+    const Fx eincl = fx_add(before, fx_incl_scan(w));
     const unsigned long long at = __ballot(fx_gt(eincl, T));
     if (lane == 0) {
         a.n_accepted[b] = k;
