@@ -177,7 +177,9 @@ int ts_decode_attn_polls(const ts_attn_shape *shape, const void *q, const void *
 
 typedef struct ts_attn_plan {
     int32_t variant;            /* kernel used: TS_VARIANT_WAVE, _TEAM or _VALU */
-    int32_t num_workers;        /* workers of the page partition */
+    int32_t num_workers;        /* workers of the page partition (as num_workers of a shape with
+                                   TS_VARIANT_AUTO it means single wavefronts, also where a worker
+                                   here is four of them) */
     int32_t combine;            /* TS_COMBINE_* */
     int32_t grid;               /* workgroups of the streaming launch (workers, then any
                                    merge workgroups) */
@@ -198,7 +200,7 @@ int ts_decode_attn_plan(const ts_attn_shape *shape, ts_attn_plan *plan);
  * until the process ends.  The call allocates nothing, on the host's HIP
  * runtime or elsewhere.  Shapes whose ts_decode_attn_workspace_size exceeds
  * the array are rejected with TS_ERR_WORKSPACE before anything is launched
- * (every shape with num_workers = 0 fits).  Every call on one GPU shares that
+ * (every shape with num_workers = 0 and TS_VARIANT_AUTO fits).  Every call on one GPU shares that
  * GPU's array, so calls that may overlap on one GPU (different streams, or
  * graphs replayed concurrently) race and must not be issued.  The array starts
  * zeroed and every call leaves its arrival counters zero, as with a
