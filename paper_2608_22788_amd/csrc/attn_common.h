@@ -45,9 +45,10 @@ constexpr int kCombineKernel = 0;    // a separate merge kernel (plain stores)
 constexpr int kCombineLast = 1;      // the last worker to finish a piece of the unit
 constexpr int kCombineInLaunch = 2;  // merge workgroups after the W workers of the grid
 
-// Polls after which a merge wavefront gives up (attn_split.h): about 6 ms,
-// longer than any call over less than 40 GB of K/V takes, and short enough for
-// a hold-up that only three overlapping calls can cause.
+// Polls after which a merge wavefront gives up (attn_split.h): some
+// milliseconds at 0.5-1 us a poll (a memory round trip), longer than a call
+// over 25 GB of K/V takes, and short enough for a hold-up that only three
+// overlapping calls can cause.
 constexpr int kMergePolls = 8192;
 
 struct AttnParams {   // 128 bytes of kernel arguments
